@@ -11,60 +11,169 @@ namespace n2v {
 
 namespace {
 
-enum : uint32_t { BAD_OFF = 1, BAD_ROW = 2, BAD_ASYM = 4, BAD_ENDS = 8 };
+enum : uint32_t { BAD_OFF = 1, BAD_ROW = 2, BAD_ASYM = 4, BAD_ENDS = 8 };  // BAD_ASYM: found on the host
 
+// Row offsets of a caller's CSR: off[0] = 0, off[n] = m, non-decreasing.  The
+// entry-parallel kernels below run only on offsets that pass.
+__global__ __launch_bounds__(256) void k_validate_off(const uint64_t *__restrict__ off, uint32_t n, uint64_t m,
+                                                      uint32_t *__restrict__ bad)
+{
+    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+    const uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t == 0 && (off[0] != 0 || off[n] != m)) atomicOr(bad, BAD_ENDS);
+    bool flag = false;
+    for (uint64_t v = t; v < n; v += stride) flag |= off[v + 1] < off[v] || off[v + 1] > m;
+    if (flag) atomicOr(bad, BAD_OFF);
+}
+
+// ------------------------------------------------------ entries and rows
+// Work over entries goes to wavefronts in chunks of CHUNK consecutive ones,
+// whatever rows they belong to: with a wavefront per row, one hub row of 60 K
+// entries (each a dependent search) outlasted all the others together
+// (k_derive 17.7 ms at R-MAT scale 20, 112 ms at scale 22 skewed), and rows of
+// ten entries left 54 lanes idle.
+constexpr uint32_t CHUNK = 1024;
+
+// Last row whose offset is at or below e (so that, offsets ascending, the row
+// that holds entry e): 64 probes a round.
+__device__ uint64_t row_of(const uint64_t *__restrict__ off, uint64_t n, uint64_t e)
+{
+    uint64_t lo = 0, hi = n + 1;  // off[lo] <= e; off[hi] > e or hi = n + 1
+    while (hi - lo > 1) {
+        const uint64_t step = (hi - lo + WAVE - 1) / WAVE;
+        const uint64_t p = lo + (uint64_t)lane_id() * step;
+        const uint64_t m = ballot(p < hi && off[p] <= e);  // a prefix of the lanes, lane 0 among them
+        const uint64_t k = (uint64_t)__popcll(m) - 1;
+        hi = lo + (k + 1) * step < hi ? lo + (k + 1) * step : hi;
+        lo += k * step;
+    }
+    return lo;
+}
+
+// mark[i] = the row that begins at entry c0 + i, SENT where none does, for
+// the chunk [c0, c0 + cnt).  Returns the row that holds c0.
+__device__ uint32_t mark_rows(const uint64_t *__restrict__ off, uint32_t n, uint64_t c0, uint32_t cnt,
+                              uint32_t *mark)
+{
+    const int l = lane_id();
+    for (uint32_t i = l; i < CHUNK; i += WAVE) mark[i] = SENT;
+    wave_lds_sync();
+    const uint64_t r0 = row_of(off, n, c0);
+    const uint64_t end = c0 + cnt;
+    uint64_t r = r0;
+    while (r < n) {
+        const uint64_t q = r + l;
+        const uint64_t o = q < n ? off[q] : end;
+        const bool in = o < end;
+        // the last of several rows with one offset is the one with entries
+        if (in && o >= c0 && off[q + 1] > o) mark[o - c0] = (uint32_t)q;
+        if (ballot(in) != ~0ull) break;
+        // a long run of rows without entries is stepped over
+        const uint64_t last = lane_val64(o, WAVE - 1);
+        r = lane_val64(o, 0) == last ? row_of(off, n, last) : r + WAVE;
+        if (lane_val64(o, 0) == last && off[r] == last) {  // that run's last row: mark it and go on behind it
+            if (l == 0 && last >= c0 && off[r + 1] > last) mark[last - c0] = (uint32_t)r;
+            r += 1;
+        }
+    }
+    wave_lds_sync();
+    return (uint32_t)r0;
+}
+
+// Inclusive running maximum of row marks over the lanes (SENT = no mark).
+__device__ __forceinline__ uint32_t row_scan(uint32_t m, uint32_t carry)
+{
+    uint32_t v = m == SENT ? 0u : m + 1u;  // rows ascend along the entries; ids are below 2^32 - 2
+    v = max(v, dpp0<0x111>(v));
+    v = max(v, dpp0<0x112>(v));
+    v = max(v, dpp0<0x114>(v));
+    v = max(v, dpp0<0x118>(v));
+    v = max(v, dpp0<0x142, 0xa>(v));
+    v = max(v, dpp0<0x143, 0xc>(v));
+    return v ? v - 1u : carry;
+}
+
+// Calls f(e, v, starts) for every entry e of the graph, v its row and
+// `starts` whether e is the row's first; whole wavefronts, lanes past the end
+// with live = false.
+template <class F>
+__device__ __forceinline__ void each_entry(const uint64_t *__restrict__ off, uint32_t n, uint64_t m, F f)
+{
+    __shared__ uint32_t marks[256 / WAVE][CHUNK];
+    uint32_t *mark = marks[threadIdx.x / WAVE];
+    const int l = lane_id();
+    const uint64_t chunks = (m + CHUNK - 1) / CHUNK;
+    const uint64_t nw = (uint64_t)gridDim.x * (256 / WAVE);
+    for (uint64_t c = (uint64_t)blockIdx.x * (256 / WAVE) + threadIdx.x / WAVE; c < chunks; c += nw) {
+        const uint64_t c0 = c * CHUNK;
+        const uint32_t cnt = m - c0 < CHUNK ? (uint32_t)(m - c0) : CHUNK;
+        uint32_t row = mark_rows(off, n, c0, cnt, mark);
+        for (uint32_t i0 = 0; i0 < cnt; i0 += WAVE) {
+            const uint32_t mk = mark[i0 + l];
+            const uint32_t v = row_scan(mk, row);
+            f(c0 + i0 + l, v, mk != SENT, i0 + l < cnt);
+            row = lane_val(v, WAVE - 1);
+        }
+        wave_lds_sync();
+    }
+}
+
+// Every row strictly ascending, without self-loops, ids below n, weights >= 1.
 __global__ __launch_bounds__(256) void k_validate(const uint64_t *__restrict__ off, const uint32_t *__restrict__ adj,
                                                   const uint16_t *__restrict__ wt, uint32_t n, uint64_t m,
                                                   uint32_t *__restrict__ bad)
 {
-    const int l = lane_id();
-    const uint64_t wave = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) / WAVE;
-    const uint64_t nw = (uint64_t)gridDim.x * blockDim.x / WAVE;
-    if (wave == 0 && l == 0 && (off[0] != 0 || off[n] != m)) atomicOr(bad, BAD_ENDS);
-    uint32_t flags = 0;
-    for (uint64_t v = wave; v < n; v += nw) {
-        const uint64_t lo = off[v], hi = off[v + 1];
-        if (hi < lo || hi > m) {
-            flags |= BAD_OFF;
-            continue;
-        }
-        for (uint64_t e = lo + l; e < hi; e += WAVE) {
-            const uint32_t x = adj[e];
-            if (x >= n || x == (uint32_t)v) flags |= BAD_ROW;
-            if (e > lo && adj[e - 1] >= x) flags |= BAD_ROW;
-            if (wt && wt[e] == 0) flags |= BAD_ROW;
-        }
-    }
-    if (flags) atomicOr(bad, flags);
+    if (*(volatile uint32_t *)bad & (BAD_OFF | BAD_ENDS)) return;
+    bool flag = false;
+    each_entry(off, n, m, [&](uint64_t e, uint32_t v, bool starts, bool live) {
+        if (!live) return;
+        const uint32_t x = adj[e];
+        flag |= x >= n || x == v;
+        flag |= !starts && adj[e - 1] >= x;
+        flag |= wt && wt[e] == 0;
+    });
+    if (flag) atomicOr(bad, BAD_ROW);
 }
 
-__global__ __launch_bounds__(256) void k_derive(const uint64_t *__restrict__ off, const uint32_t *__restrict__ adj,
-                                                const uint16_t *__restrict__ wt, uint32_t n, VRec *__restrict__ vrec,
-                                                uint2 *__restrict__ erec, uint64_t *__restrict__ wsum,
-                                                uint32_t *__restrict__ bad, uint32_t *__restrict__ wrange,
-                                                int check_sym)
+// Vertex records of an unweighted graph.
+__global__ __launch_bounds__(256) void k_vrec(const uint64_t *__restrict__ off, uint32_t n, VRec *__restrict__ vrec)
+{
+    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+    for (uint64_t v = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += stride) {
+        const uint64_t lo = off[v], d = off[v + 1] - lo;
+        VRec r;
+        r.off = lo;
+        r.deg = (uint32_t)d;
+        r.wmax = d ? 1u : 0u;
+        vrec[v] = r;
+    }
+}
+
+// Vertex records, row weight sums and the graph's weight range (wrange[0] =
+// max(0xFFFF - w), wrange[1] = max(w)): a wavefront per row, its weights four
+// to a lane and round (1.6 ms at R-MAT scale 20; eight measured the same).
+__global__ __launch_bounds__(256) void k_vrec_w(const uint64_t *__restrict__ off, const uint16_t *__restrict__ wt,
+                                                uint32_t n, VRec *__restrict__ vrec, uint64_t *__restrict__ wsum,
+                                                uint32_t *__restrict__ wrange)
 {
     const int l = lane_id();
     const uint64_t wave = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) / WAVE;
     const uint64_t nw = (uint64_t)gridDim.x * blockDim.x / WAVE;
-    uint32_t flags = 0;
-    // graph-wide weight range: wrange[0] = max(0xFFFF - w), wrange[1] = max(w)
     uint32_t winv = 0, wall = 0;
     for (uint64_t v = wave; v < n; v += nw) {
         const uint64_t lo = off[v], hi = off[v + 1];
         uint32_t wm = 0;
         uint64_t ws = 0;
-        for (uint64_t e = lo + l; e < hi; e += WAVE) {
-            const uint32_t x = adj[e];
-            const uint64_t xlo = off[x], xhi = off[x + 1];
-            const uint64_t p = lower_bound_g(adj, xlo, xhi, (uint32_t)v);
-            const bool found = p < xhi && adj[p] == (uint32_t)v;
-            if (!found && check_sym) flags |= BAD_ASYM;
-            erec[e] = make_uint2(x, found ? (uint32_t)(p - xlo) : SENT);
-            const uint32_t w = wt ? wt[e] : 1u;
-            wm = w > wm ? w : wm;
-            winv = 0xFFFFu - w > winv ? 0xFFFFu - w : winv;
-            ws += w;
+        for (uint64_t e = lo + l; e < hi; e += 4 * WAVE) {
+            uint32_t w[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) w[k] = e + k * WAVE < hi ? wt[e + k * WAVE] : 0u;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                wm = w[k] > wm ? w[k] : wm;
+                if (e + k * WAVE < hi) winv = 0xFFFFu - w[k] > winv ? 0xFFFFu - w[k] : winv;
+                ws += w[k];
+            }
         }
 #pragma unroll
         for (int msk = 32; msk >= 1; msk >>= 1) {
@@ -77,9 +186,9 @@ __global__ __launch_bounds__(256) void k_derive(const uint64_t *__restrict__ off
             VRec r;
             r.off = lo;
             r.deg = (uint32_t)(hi - lo);
-            r.wmax = hi > lo ? wm : 0u;
+            r.wmax = wm;
             vrec[v] = r;
-            if (wsum) wsum[v] = ws;
+            wsum[v] = ws;
         }
     }
 #pragma unroll
@@ -87,11 +196,48 @@ __global__ __launch_bounds__(256) void k_derive(const uint64_t *__restrict__ off
         const uint32_t o = __shfl_xor(winv, msk, WAVE);
         winv = o > winv ? o : winv;
     }
+    // most wavefronts find the range already as wide as theirs: one address
+    // takes few atomics
     if (l == 0) {
-        if (winv) atomicMax(wrange, winv);
-        if (wall) atomicMax(wrange + 1, wall);
+        if (winv > *(volatile uint32_t *)wrange) atomicMax(wrange, winv);
+        if (wall > *(volatile uint32_t *)(wrange + 1)) atomicMax(wrange + 1, wall);
     }
-    if (flags) atomicOr(bad, flags);
+}
+
+// Entry records, reverse positions still unknown (SENT).
+__global__ __launch_bounds__(256) void k_erec(const uint32_t *__restrict__ adj, uint64_t m, uint2 *__restrict__ erec)
+{
+    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+    for (uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < m; e += stride)
+        erec[e] = make_uint2(adj[e], SENT);
+}
+
+// Reverse positions.  Of the two entries of an edge, the one whose target has
+// the shorter row (ties: the smaller id) searches its own row's vertex there
+// and writes both positions: half the searches, none of them in a hub's row
+// from a leaf.  Bound by the random lines of the searches and of the partners'
+// 4-byte writes.  Counts the entries that found a partner.
+__global__ __launch_bounds__(256) void k_reverse(const uint64_t *__restrict__ off, const uint32_t *__restrict__ adj,
+                                                 uint32_t n, uint64_t m, uint2 *__restrict__ erec,
+                                                 unsigned long long *__restrict__ paired)
+{
+    uint64_t found = 0;
+    each_entry(off, n, m, [&](uint64_t e, uint32_t v, bool, bool live) {
+        if (!live) return;
+        const uint32_t x = adj[e];
+        const uint64_t vlo = off[v], xlo = off[x], xhi = off[x + 1];
+        const uint64_t dv = off[v + 1] - vlo, dx = xhi - xlo;
+        if (dx < dv || (dx == dv && x < v)) {
+            const uint64_t p = lower_bound_g(adj, xlo, xhi, v);
+            if (p < xhi && adj[p] == v) {
+                erec[e].y = (uint32_t)(p - xlo);
+                erec[p].y = (uint32_t)(e - vlo);
+                found += 2;
+            }
+        }
+    });
+    found = wave_sum(found);
+    if (lane_id() == 0 && found) atomicAdd(paired, (unsigned long long)found);
 }
 
 // Sketch words of a vertex of degree d: d rows of memo_row_words(d).
@@ -204,6 +350,20 @@ size_t graph_layout(uint32_t n, uint64_t m, int weighted, void *ws, size_t ws_by
     return c.total();
 }
 
+uint32_t grid_for_threads(uint64_t count)
+{
+    const uint64_t blocks = (count + 255) / 256;
+    return (uint32_t)(blocks > 65536 ? 65536 : (blocks < 1 ? 1 : blocks));
+}
+
+// Blocks of each_entry: four chunks at once per block, no more than twice what
+// 256 CUs hold (each wavefront ends with one atomic on one address).
+uint32_t grid_for_entries(uint64_t m)
+{
+    const uint64_t blocks = (m + 4 * CHUNK - 1) / (4 * CHUNK);
+    return (uint32_t)(blocks > 4096 ? 4096 : (blocks < 1 ? 1 : blocks));
+}
+
 uint32_t grid_for_waves(uint64_t waves)
 {
     uint64_t blocks = (waves + 3) / 4;
@@ -256,7 +416,8 @@ extern "C" int n2v_graph_create(const uint64_t *off, const uint32_t *adj, const 
     hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, st, L.status, 64u);
     N2V_HIP(hipGetLastError());
     if (o.validate >= 1) {
-        hipLaunchKernelGGL(k_validate, dim3(grid_for_waves(n)), dim3(256), 0, st, off, adj, wt, n, m, L.status + 1);
+        hipLaunchKernelGGL(k_validate_off, dim3(grid_for_threads(n)), dim3(256), 0, st, off, n, m, L.status + 1);
+        hipLaunchKernelGGL(k_validate, dim3(grid_for_entries(m)), dim3(256), 0, st, off, adj, wt, n, m, L.status + 1);
         N2V_HIP(hipGetLastError());
         uint32_t bad = 0;
         N2V_HIP(hipMemcpyAsync(&bad, L.status + 1, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
@@ -267,14 +428,21 @@ extern "C" int n2v_graph_create(const uint64_t *off, const uint32_t *adj, const 
                              "id/weight, 8 off[0] or off[n])",
                              bad);
     }
-    hipLaunchKernelGGL(k_derive, dim3(grid_for_waves(n)), dim3(256), 0, st, off, adj, wt, n, L.vrec, L.erec, L.wsum,
-                       L.status + 1, L.status + 2, o.validate >= 2 ? 1 : 0);
+    if (wt)
+        hipLaunchKernelGGL(k_vrec_w, dim3(std::min(grid_for_waves(n), 4096u)), dim3(256), 0, st, off, wt, n, L.vrec, L.wsum,
+                           L.status + 2);
+    else
+        hipLaunchKernelGGL(k_vrec, dim3(grid_for_threads(n)), dim3(256), 0, st, off, n, L.vrec);
+    hipLaunchKernelGGL(k_erec, dim3(grid_for_threads(m)), dim3(256), 0, st, adj, m, L.erec);
+    hipLaunchKernelGGL(k_zero_u64w, dim3(1), dim3(64), 0, st, L.hist, 1u);
+    hipLaunchKernelGGL(k_reverse, dim3(grid_for_entries(m)), dim3(256), 0, st, off, adj, n, m, L.erec, L.hist);
     N2V_HIP(hipGetLastError());
     if (o.validate >= 2) {
-        uint32_t bad = 0;
-        N2V_HIP(hipMemcpyAsync(&bad, L.status + 1, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
+        unsigned long long paired = 0;
+        N2V_HIP(hipMemcpyAsync(&paired, L.hist, sizeof(paired), hipMemcpyDeviceToHost, st));
         N2V_HIP(hipStreamSynchronize(st));
-        if (bad) return set_error(N2V_EGRAPH, "n2v_graph_create: CSR is not symmetric (flags 0x%x)", bad);
+        if (paired != m)
+            return set_error(N2V_EGRAPH, "n2v_graph_create: CSR is not symmetric (flags 0x%x)", (unsigned)BAD_ASYM);
     }
     const uint64_t memo_min = (uint64_t)o.d_rule + 1;
     hipLaunchKernelGGL(k_hub_len, dim3(grid_for_waves(n)), dim3(256), 0, st, off, n, memo_min, wt != nullptr,

@@ -151,7 +151,25 @@ __global__ __launch_bounds__(WAVE) void k_dd_write(const uint64_t *__restrict__ 
                 const R4 q = philox(k0, k1, lo, hi, 0u, 2u);
                 wt[pos] = (uint16_t)(1u + (uint32_t)(((uint64_t)q.x * 1000u) >> 32));
             }
-            atomicAdd(&deg[u], 1ull);
+        }
+        // row lengths: the kept entries of one row lie together, so the lane
+        // that ends a row's run in this round adds the whole run (an addition
+        // per entry serialised on the hub rows' counters: 4.4 ms of a scale-20
+        // build)
+        if (m) {
+            const uint32_t u = (uint32_t)(k >> scale);
+            const uint64_t above = m & ~lanemask_lt() & ~(1ull << l);  // kept lanes after this one
+            const uint64_t below = m & lanemask_lt();
+            const uint32_t un = shfl32(u, above ? first_lane(above) : l);
+            const uint32_t up = shfl32(u, below ? 63 - __clzll((long long)below) : l);
+            const bool first = keep && (!below || up != u), last = keep && (!above || un != u);
+            const uint64_t firsts = ballot(first);
+            if (last) {
+                const uint64_t fb = firsts & (lanemask_lt() | (1ull << l));
+                const int f = 63 - __clzll((long long)fb);
+                const uint64_t span = m & (lanemask_lt() | (1ull << l)) & ~((1ull << f) - 1ull);
+                atomicAdd(&deg[u], (unsigned long long)__popcll(span));
+            }
         }
         run += __popcll(m);
     }
