@@ -72,6 +72,7 @@ struct DevGraph {
     const VRec *vrec;      // n
     const uint2 *erec;     // m: (neighbour x, position of the reverse entry in N(x) or SENT)
     const uint32_t *adj;   // m, rows strictly ascending
+    const uint64_t *filt;  // membership filter of every row (see filter_word), or null
     const uint16_t *wt;    // m, or null for an unweighted graph
     const uint64_t *wsum;  // n: row weight sums (weighted graphs only)
     const uint64_t *hbase; // n+1: u16 word offset of the sketch rows of each vertex of degree >= memo_min
@@ -235,6 +236,35 @@ __device__ __forceinline__ bool contains_g(const uint32_t *__restrict__ a, uint6
 {
     const uint64_t p = lower_bound_g(a, lo, hi, x);
     return p < hi && a[p] == x;
+}
+
+// ------------------------------------------------- membership filter
+// "Is x a neighbour of t?" is mostly answered no, and a binary search spends
+// several dependent random lines on it.  A Bloom filter of 16 bits per entry
+// answers most of those with one 8-byte read: the row at entries [off, off +
+// d) owns the 64-bit words off / 4 .. (off + d - 1) / 4 (neighbouring rows
+// share the words at their ends, which only adds bits), x sets four bits of
+// one of them.  About 0.5% of the strangers pass (four bits of a word that
+// holds four entries on average) and go on to the search, as members do.
+constexpr uint64_t FILTER_MAX_ENTRIES = 1ull << 33;  // larger graphs leave the 2 bytes per entry to their sketches
+
+__host__ __device__ inline uint64_t filter_words(uint64_t m) { return m / 4 + 1; }
+
+// Word of x in the filter of the row of d >= 1 entries at off.
+__device__ __forceinline__ uint64_t filter_word(uint64_t off, uint32_t d, uint32_t x)
+{
+    const uint64_t w0 = off >> 2;
+    const uint32_t words = (uint32_t)(((off + d - 1) >> 2) - w0) + 1;
+    return w0 + __umulhi(x * 0x9E3779B1u, words);
+}
+
+// Bits of x in its word.
+__device__ __forceinline__ uint64_t filter_bits(uint32_t x)
+{
+    const uint32_t h = (x ^ (x >> 15)) * 0x85EBCA6Bu;
+    const uint32_t lo = (1u << (h >> 27)) | (1u << ((h >> 22) & 31u));
+    const uint32_t hi = (1u << ((h >> 17) & 31u)) | (1u << ((h >> 12) & 31u));
+    return join64(hi, lo);
 }
 
 }  // namespace n2v

@@ -204,12 +204,21 @@ __global__ __launch_bounds__(256) void k_vrec_w(const uint64_t *__restrict__ off
     }
 }
 
-// Entry records, reverse positions still unknown (SENT).
-__global__ __launch_bounds__(256) void k_erec(const uint32_t *__restrict__ adj, uint64_t m, uint2 *__restrict__ erec)
+// Entry records, reverse positions still unknown (SENT), and the rows'
+// membership filters (cleared before; null: none).
+__global__ __launch_bounds__(256) void k_entries(const uint64_t *__restrict__ off, const uint32_t *__restrict__ adj,
+                                                 uint32_t n, uint64_t m, uint2 *__restrict__ erec,
+                                                 unsigned long long *__restrict__ filt)
 {
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < m; e += stride)
-        erec[e] = make_uint2(adj[e], SENT);
+    each_entry(off, n, m, [&](uint64_t e, uint32_t v, bool, bool live) {
+        if (!live) return;
+        const uint32_t x = adj[e];
+        erec[e] = make_uint2(x, SENT);
+        if (filt) {
+            const uint64_t lo = off[v];
+            atomicOr(filt + filter_word(lo, (uint32_t)(off[v + 1] - lo), x), (unsigned long long)filter_bits(x));
+        }
+    });
 }
 
 // Reverse positions.  Of the two entries of an edge, the one whose target has
@@ -238,6 +247,12 @@ __global__ __launch_bounds__(256) void k_reverse(const uint64_t *__restrict__ of
     });
     found = wave_sum(found);
     if (lane_id() == 0 && found) atomicAdd(paired, (unsigned long long)found);
+}
+
+__global__ void k_fill0_u64(uint64_t *p, uint64_t n)
+{
+    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = 0;
 }
 
 // Sketch words of a vertex of degree d: d rows of memo_row_words(d).
@@ -328,6 +343,7 @@ __global__ void k_zero_u32(uint32_t *p, uint32_t n)
 struct GraphLayout {
     VRec *vrec;
     uint2 *erec;
+    uint64_t *filt;
     uint64_t *wsum;
     uint64_t *hbase;
     void *scan;
@@ -343,6 +359,7 @@ size_t graph_layout(uint32_t n, uint64_t m, int weighted, void *ws, size_t ws_by
     L->cursors = c.take<uint32_t>((uint64_t)CURSOR_SLOTS * CURSOR_STRIDE);
     L->vrec = c.take<VRec>((uint64_t)n + 1);
     L->erec = c.take<uint2>(m ? m : 1);
+    L->filt = m <= FILTER_MAX_ENTRIES ? c.take<uint64_t>(filter_words(m)) : nullptr;
     L->wsum = weighted ? c.take<uint64_t>((uint64_t)n + 1) : nullptr;
     L->hbase = c.take<uint64_t>((uint64_t)n + 1);
     L->scan = c.take<char>(scan_scratch_bytes((uint64_t)n + 1));
@@ -433,7 +450,11 @@ extern "C" int n2v_graph_create(const uint64_t *off, const uint32_t *adj, const 
                            L.status + 2);
     else
         hipLaunchKernelGGL(k_vrec, dim3(grid_for_threads(n)), dim3(256), 0, st, off, n, L.vrec);
-    hipLaunchKernelGGL(k_erec, dim3(grid_for_threads(m)), dim3(256), 0, st, adj, m, L.erec);
+    if (L.filt)
+        hipLaunchKernelGGL(k_fill0_u64, dim3(grid_for_threads(filter_words(m))), dim3(256), 0, st, L.filt,
+                           filter_words(m));
+    hipLaunchKernelGGL(k_entries, dim3(grid_for_entries(m)), dim3(256), 0, st, off, adj, n, m, L.erec,
+                       (unsigned long long *)L.filt);
     hipLaunchKernelGGL(k_zero_u64w, dim3(1), dim3(64), 0, st, L.hist, 1u);
     hipLaunchKernelGGL(k_reverse, dim3(grid_for_entries(m)), dim3(256), 0, st, off, adj, n, m, L.erec, L.hist);
     N2V_HIP(hipGetLastError());
@@ -479,6 +500,7 @@ extern "C" int n2v_graph_create(const uint64_t *off, const uint32_t *adj, const 
     g->dg.vrec = L.vrec;
     g->dg.erec = L.erec;
     g->dg.adj = adj;
+    g->dg.filt = L.filt;
     g->dg.wt = wt;
     g->dg.wsum = L.wsum;
     g->dg.status = L.status;

@@ -149,6 +149,47 @@ __device__ __forceinline__ void emit(const JobCtx &J, uint32_t i, uint32_t col, 
     }
 }
 
+// A walk's latest entries, on their way to its row: a 4-byte store per move
+// leaves L2 as a partial line of its own long before the row's next one comes
+// (ER-22: 1.8 write requests per move), so a lane stores four at once.
+struct Cols {
+    uint32_t c[4];  // the last n entries, the newest in c[3]
+    uint32_t n;
+};
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4), aligned(4)));
+
+// Stores the entries of columns (col - n, col] of walk i.
+template <bool WALKS>
+__device__ __forceinline__ void flush(const JobCtx &J, uint32_t i, uint32_t col, Cols &b)
+{
+    if (!WALKS || b.n == 0) return;
+    uint32_t *p = J.out + (uint64_t)i * (J.L + 1) + col;
+    if (b.n == 4) {
+        *(u32x4 *)(p - 3) = u32x4{b.c[0], b.c[1], b.c[2], b.c[3]};
+    } else {
+        p[0] = b.c[3];
+        if (b.n > 1) p[-1] = b.c[2];
+        if (b.n > 2) p[-2] = b.c[1];
+    }
+    b.n = 0;
+}
+
+// emit() through the buffer: stored when the entry ends a group of four of
+// the output array.
+template <bool WALKS, bool COUNTS>
+__device__ __forceinline__ void put(const JobCtx &J, uint32_t i, uint32_t col, uint32_t x, Cols &b, uint64_t &csum)
+{
+    if (COUNTS) emit<false, true>(J, i, col, x, csum);
+    if (!WALKS) return;
+    b.c[0] = b.c[1];
+    b.c[1] = b.c[2];
+    b.c[2] = b.c[3];
+    b.c[3] = x;
+    b.n += 1;
+    if (((i * (J.L + 1) + col) & 3u) == 3u) flush<WALKS>(J, i, col, b);
+}
+
 // v's record; a hub move also takes v's first sketch row in the same round
 // trip, which its sketch lookup would otherwise wait for
 template <bool HUB = false>
@@ -187,104 +228,101 @@ __device__ __forceinline__ void advance(const Exec &E, WS &st, uint32_t j, uint3
     st.s += 1;
 }
 
-// Rejection attempt k up to the membership test: the proposal j and, unless
-// the outcome is already forced, the proposal x and the acceptance draw u
-// against A * w (A = A_COM if x is a neighbour of t, else A_out).  Returns
-// 1 (accept), 0 (reject) or 2 (the test is needed).
+// floor((hi 2^32 + lo) y / 2^64) of a 64-bit draw and a 32-bit bound.
+__device__ __forceinline__ uint32_t hi64_32(uint32_t hi, uint32_t lo, uint32_t y)
+{
+    const uint64_t t = (uint64_t)lo * y >> 32;
+    return (uint32_t)(((uint64_t)hi * y + t) >> 32);
+}
+
+// Rejection attempt k up to the membership test: the proposal j, the
+// acceptance draw u and the weight w of j.  Returns 1 (accept), 0 (reject) or
+// 2 (accept iff u < A w with A = A_COM if the proposal is a neighbour of t,
+// else A_out).
 struct Att {
-    uint32_t j, x;
-    uint64_t u, w;
+    uint32_t j, u, w;
 };
 
 __device__ __forceinline__ int attempt_pre(const Exec &E, const JobCtx &J, const WS &st, uint32_t k, Att &a)
 {
     const bool first = st.s == 0;
-    const uint64_t E_env = (uint64_t)st.vw * (first ? 1u : amax3(J));
     const R4 r = philox(J.k0, J.k1, J.wbase + st.i, st.s, k, 0u);
-    const uint64_t j = hi64(join64(r.x, r.y), st.vd);
-    a.j = (uint32_t)j;
-    a.u = hi64(join64(r.z, r.w), E_env);
-    a.w = E.g.wt ? E.g.wt[st.vo + j] : 1u;
+    a.j = hi64_32(r.x, r.y, st.vd);
+    const uint32_t amax = amax3(J);  // a power of two, as every multiplier is
+    if (E.g.wt) {
+        a.u = hi64_32(r.z, r.w, st.vw * (first ? 1u : amax));
+        a.w = E.g.wt[st.vo + a.j];
+    } else {
+        a.u = first ? 0u : r.z >> (1 + __clz(amax));  // R2 amax / 2^64
+        a.w = 1;
+    }
     const uint32_t acmin = A_COM < J.A_out ? A_COM : J.A_out;
     const uint32_t acmax = A_COM < J.A_out ? J.A_out : A_COM;
     if (first) return a.u < a.w;
-    if (j == st.pos_t) return a.u < J.A_ret * a.w;
+    if (a.j == st.pos_t) return a.u < J.A_ret * a.w;
     if (a.u < acmin * a.w) return 1;
-    if (a.u >= acmax * a.w) return 0;
-    a.x = E.g.adj[st.vo + j];
-    return 2;
+    return a.u < acmax * a.w ? 2 : 0;
 }
 
-// One rejection attempt k; returns whether it accepts and its neighbour index.
-__device__ __forceinline__ bool attempt(const Exec &E, const JobCtx &J, const WS &st, uint32_t k, uint32_t &j_out)
+// Whether x may be a neighbour of t; false is certain.
+__device__ __forceinline__ bool maybe_member(const Exec &E, const WS &st, uint32_t x)
+{
+    if (!E.g.filt) return true;
+    const uint64_t b = filter_bits(x);
+    return (E.g.filt[filter_word(st.to, st.td, x)] & b) == b;
+}
+
+// Whether x is a neighbour of t.
+__device__ __forceinline__ bool is_member(const Exec &E, const WS &st, uint32_t x)
+{
+    return maybe_member(E, st, x) && contains_g(E.g.adj, st.to, st.to + st.td, x);
+}
+
+// One rejection attempt k; returns whether it accepts, its neighbour index,
+// and, accepted, that neighbour and the position of v in its row.  The entry
+// record that the test reads for x serves the accepted move too.
+__device__ __forceinline__ bool attempt(const Exec &E, const JobCtx &J, const WS &st, uint32_t k, uint32_t &j_out,
+                                        uint32_t &x, uint32_t &rev)
 {
     Att a;
     const int r = attempt_pre(E, J, st, k, a);
     j_out = a.j;
-    if (r < 2) return r == 1;
-    const bool com = contains_g(E.g.adj, st.to, st.to + st.td, a.x);
-    return a.u < (uint64_t)(com ? A_COM : J.A_out) * a.w;
-}
-
-// x in the sorted LDS array T[0, n): a branchless lower bound (the bound lies
-// in [p, p + len - 1] throughout), then one compare.
-__device__ __forceinline__ bool lds_contains(const uint32_t *T, uint32_t n, uint32_t x)
-{
-    const uint32_t *q = T;
-    for (uint32_t len = n; len > 1; len -= len >> 1) {
-        const uint32_t half = len >> 1;
-        q += q[half - 1] < x ? half : 0u;
-    }
-    return n > 0 && *q == x;
+    if (r == 0) return false;
+    resolve(E, st, a.j, x, rev);
+    if (r == 1) return true;
+    return a.u < (is_member(E, st, x) ? A_COM : J.A_out) * a.w;
 }
 
 // Thread class: attempts in order until one accepts (false after a_cap, or
 // after the first kmax attempts).
-__device__ bool thread_reject(const Exec &E, const JobCtx &J, const WS &st, uint32_t &j_out,
-                              uint32_t kmax = 0xFFFFFFFFu)
+__device__ bool thread_reject(const Exec &E, const JobCtx &J, const WS &st, uint32_t &j_out, uint32_t &x,
+                              uint32_t &rev, uint32_t kmax = 0xFFFFFFFFu)
 {
     const uint32_t n = kmax < E.g.a_cap ? kmax : E.g.a_cap;
     for (uint32_t k = 0; k < n; ++k)
-        if (attempt(E, J, st, k, j_out)) return true;
+        if (attempt(E, J, st, k, j_out, x, rev)) return true;
     return false;
 }
 
 // Wave class: lanes take attempts k0 + lane (from attempt kfrom on, the
 // earlier ones having rejected); the lowest accepting one wins.
-// When some attempt needs "is x a neighbour of t?" and N(t) fits, the wave
-// stages N(t) in LDS once (one coalesced read) and searches it there.
-__device__ bool wave_reject(const Exec &E, const JobCtx &J, const WS &st_in, HubLds &L, uint32_t &j_out,
-                            uint32_t kfrom = 0)
+__device__ bool wave_reject(const Exec &E, const JobCtx &J, const WS &st_in, uint32_t &j_out, uint32_t &x_out,
+                            uint32_t &rev_out, uint32_t kfrom = 0)
 {
     const WS st = uniform_ws(st_in);
-    const int l = lane_id();
-    bool staged = false;
     for (uint32_t k0 = kfrom; k0 < E.g.a_cap; k0 += WAVE) {
-        const uint32_t k = k0 + l;
-        Att a;
-        a.j = 0;
-        const int r = k < E.g.a_cap ? attempt_pre(E, J, st, k, a) : 0;
-        bool acc = r == 1;
-        if (ballot(r == 2)) {
-            if (!staged && st.td <= (uint32_t)SPCAP) {
-                for (uint32_t i = l; i < st.td; i += WAVE) L.a.sp.pos[i] = E.g.adj[st.to + i];
-                wave_lds_sync();
-                staged = true;
-            }
-            if (r == 2) {
-                const bool com = staged ? lds_contains(L.a.sp.pos, st.td, a.x)
-                                        : contains_g(E.g.adj, st.to, st.to + st.td, a.x);
-                acc = a.u < (uint64_t)(com ? A_COM : J.A_out) * a.w;
-            }
-        }
+        const uint32_t k = k0 + lane_id();
+        uint32_t j = 0, x = 0, rev = 0;
+        const bool acc = k < E.g.a_cap && attempt(E, J, st, k, j, x, rev);
         const uint64_t m = ballot(acc);
         if (m) {
-            j_out = lane_val(a.j, first_lane(m));
-            wave_lds_sync();
+            const int f = first_lane(m);
+            j_out = lane_val(j, f);
+            x_out = lane_val(x, f);
+            rev_out = lane_val(rev, f);
             return true;
         }
     }
-    wave_lds_sync();
     return false;
 }
 
@@ -1398,15 +1436,17 @@ constexpr int POOL = 256;  // most walks a wavefront claims per atomic
 // Walk slot of one lane, kept in LDS between the thread and wave phases so
 // that neither phase holds the other's registers.
 struct Slot {
-    uint32_t job, i, s, v, t, pos_t, jprev;
-    uint32_t flags;  // bit 0: live, bit 1: pending wave/hub move, bit 2: after a_cap rejections
+    uint32_t i, s, v, t, pos_t, jprev;
+    uint32_t k;      // rejections of the current move so far
+    uint32_t flags;  // bit 0: live, bit 1: pending wave/hub move, bit 2: after a_cap rejections; from bit 8: job
 };
-enum : uint32_t { SL_LIVE = 1, SL_PEND = 2, SL_CAP = 4 };
+enum : uint32_t { SL_LIVE = 1, SL_PEND = 2, SL_CAP = 4, SL_JOB = 8 };
+static_assert(MAX_TABLE_JOBS <= 1u << 24, "a job index fits above the slot's flags");
 
 template <bool HUB = false>
 __device__ __forceinline__ void slot_to_ws(const Exec &E, const Slot &q, WS &st)
 {
-    st.job = q.job;
+    st.job = q.flags >> SL_JOB;
     st.i = q.i;
     st.s = q.s;
     st.t = q.t;
@@ -1423,16 +1463,16 @@ __device__ __forceinline__ void slot_to_ws(const Exec &E, const Slot &q, WS &st)
     }
 }
 
-__device__ __forceinline__ void ws_to_slot(const WS &st, uint32_t flags, Slot &q)
+__device__ __forceinline__ void ws_to_slot(const WS &st, uint32_t flags, uint32_t k, Slot &q)
 {
-    q.job = st.job;
     q.i = st.i;
     q.s = st.s;
     q.v = st.v;
     q.t = st.t;
     q.pos_t = st.pos_t;
     q.jprev = st.jprev;
-    q.flags = flags;
+    q.k = k;
+    q.flags = flags | (st.job << SL_JOB);
 }
 
 // The graph view a kernel instantiated for unweighted graphs (WT false)
@@ -1478,7 +1518,7 @@ __global__ __launch_bounds__(PBLOCK, 5) void k_persistent(Exec E_arg, Src S)
             WS st;
             bool live = q.flags & SL_LIVE;
             bool pend = q.flags & SL_PEND;
-            uint32_t cap = q.flags & SL_CAP;
+            uint32_t cap = q.flags & SL_CAP, k = live ? q.k : 0u;
             if (live) slot_to_ws(E, q, st);
             // idle lanes start walks claimed from the global counter, pool at a time
             for (;;) {
@@ -1508,35 +1548,53 @@ __global__ __launch_bounds__(PBLOCK, 5) void k_persistent(Exec E_arg, Src S)
                     live = start_walk<WALKS, COUNTS>(E, J, job, i, S.start(job, i), st, csum);
                     pend = false;
                     cap = 0;
+                    k = 0;
                 }
                 const uint32_t took = __popcll(m);
                 pool_next += took < avail ? took : avail;
             }
             if (ballot(live) == 0) break;
-            for (uint32_t it = 0; it < E.thread_iters; ++it) {
-                if (live && !pend && st.vd > tw) pend = true;
+            // Rejection attempts: every round each lane makes the next attempt
+            // of its own move, and a lane that accepts goes on to its next move
+            // at once.  A round per move held every lane to the wave's longest
+            // chain: 14.5 attempts where a lane needs 3.9 at p = 1/2, q = 2.
+            // Bound by random 128-byte lines: per move a record, its vertex
+            // record and, per tested proposal, a record and a filter word.
+            // With the filter, the records read once and four entries per
+            // store: ER-22 (2, 1/2) 24.2 -> 15.5 ms, WeC-22 (1/2, 2) 67.7 ->
+            // 27.5 ms, FN-Approx on Skew-5 158 -> 108 ms, a server's 48 requests
+            // 30.2 -> 27 ms.
+            if (live && st.vd > tw) pend = true;
+            Cols cb;
+            cb.n = 0;
+            JobCtx J = S.ctx(live ? st.job : 0u);
+            for (uint32_t it = 0;; ++it) {
                 const bool can = live && !pend;
-                if (ballot(can) == 0) break;
-                if (can) {
-                    const JobCtx J = S.ctx(st.job);
-                    uint32_t j;
-                    if (thread_reject(E, J, st, j)) {
-                        uint32_t x, rev;
-                        resolve(E, st, j, x, rev);
-                        emit<WALKS, COUNTS>(J, st.i, st.s + 1, x, csum);
-                        advance(E, st, j, x, rev);
-                        if (st.s == J.L || st.vd == 0) {
-                            fill_tail_lane<WALKS>(J, st.i, st.s);
-                            live = false;
-                        }
-                    } else {
+                const uint64_t act = ballot(can);
+                if (act == 0) break;
+                // past the budget, back to the wave phase and to claiming as
+                // soon as some lane waits for either
+                if (it >= E.thread_iters && act != ~0ull && (!exhausted || ballot(pend))) break;
+                if (!can) continue;
+                uint32_t j, x, rev;
+                if (attempt(E, J, st, k, j, x, rev)) {
+                    put<WALKS, COUNTS>(J, st.i, st.s + 1, x, cb, csum);
+                    advance(E, st, j, x, rev);
+                    k = 0;
+                    if (st.s == J.L || st.vd == 0) {
+                        flush<WALKS>(J, st.i, st.s, cb);
+                        fill_tail_lane<WALKS>(J, st.i, st.s);
+                        live = false;
+                    } else if (st.vd > tw) {
                         pend = true;
-                        cap = SL_CAP;
                     }
+                } else if (++k >= E.g.a_cap) {
+                    pend = true;
+                    cap = SL_CAP;
                 }
             }
-            if (live && !pend) pend = st.vd > tw;
-            if (live) ws_to_slot(st, SL_LIVE | (pend ? SL_PEND : 0) | cap, q);
+            if (live) flush<WALKS>(J, st.i, st.s, cb);
+            if (live) ws_to_slot(st, SL_LIVE | (pend ? SL_PEND : 0) | cap, k, q);
             else q.flags = 0;
             sl[l] = q;
         }
@@ -1547,13 +1605,13 @@ __global__ __launch_bounds__(PBLOCK, 5) void k_persistent(Exec E_arg, Src S)
             const int o = first_lane(pm);
             pm &= pm - 1;
             Slot q;
-            q.job = uni(sl[o].job);
             q.i = uni(sl[o].i);
             q.s = uni(sl[o].s);
             q.v = uni(sl[o].v);
             q.t = uni(sl[o].t);
             q.pos_t = uni(sl[o].pos_t);
             q.jprev = uni(sl[o].jprev);
+            q.k = 0;
             q.flags = uni(sl[o].flags);
             WS w;
             slot_to_ws<true>(E, q, w);
@@ -1562,16 +1620,17 @@ __global__ __launch_bounds__(PBLOCK, 5) void k_persistent(Exec E_arg, Src S)
             bool capped = q.flags & SL_CAP;
             bool alive = true;
             for (;;) {
-                uint32_t j = 0, kidx = capped ? E.g.a_cap : 0u;
+                uint32_t j = 0, x, rev, kidx = capped ? E.g.a_cap : 0u;
                 bool icdf = capped || w.vd > E.g.d_rule;
-                if (!icdf && !wave_reject(E, J, w, L, j)) {
+                if (!icdf && !wave_reject(E, J, w, j, x, rev)) {
                     icdf = true;
                     kidx = E.g.a_cap;
                 }
                 uint32_t xj = SENT;
                 if (icdf) j = wave_inverse_cdf(E, J, w, kidx, L, xj);
-                uint32_t x, rev;
-                if (xj != SENT && !(w.s > 0 && j == w.pos_t)) {
+                if (!icdf) {
+                    // the accepting lane's entry is known
+                } else if (xj != SENT && !(w.s > 0 && j == w.pos_t)) {
                     // the neighbour is known: its record and the reverse
                     // position load together
                     x = xj;
@@ -1595,7 +1654,7 @@ __global__ __launch_bounds__(PBLOCK, 5) void k_persistent(Exec E_arg, Src S)
             wave_lds_sync();
             if (l == o) {
                 Slot r;
-                if (alive) ws_to_slot(w, SL_LIVE, r);
+                if (alive) ws_to_slot(w, SL_LIVE, 0, r);
                 else r.flags = 0;
                 sl[o] = r;
             }
@@ -1649,11 +1708,9 @@ __device__ __forceinline__ bool plain_load(const Exec &E, const uint4 &q, uint32
 }
 
 template <bool WALKS, bool COUNTS>
-__device__ __forceinline__ void plain_finish(const Exec &E, const JobCtx &J, WS &st, uint32_t j, uint4 *state,
-                                             uint64_t &csum, bool wave)
+__device__ __forceinline__ void plain_finish(const JobCtx &J, WS &st, uint32_t j, uint32_t x, uint32_t rev,
+                                             uint4 *state, uint64_t &csum, bool wave)
 {
-    uint32_t x, rev;
-    resolve(E, st, j, x, rev);
     if (!wave || lane_id() == 0) emit<WALKS, COUNTS>(J, st.i, st.s + 1, x, csum);
     // a dead end at x is found by the next superstep, which loads x's record
     // anyway
@@ -1694,9 +1751,9 @@ __global__ __launch_bounds__(256) void k_plain_step(Exec E, OneJob S, uint32_t s
                         st.vd <= MEMO_MAX_DEG && sketch_row(E, st, st.pos_t)[0] != 0);
                 push = !big;
             } else {
-                uint32_t j;
-                if (thread_reject(E, S.c, st, j, COOP ? PLAIN_LANE_ATTEMPTS : 0xFFFFFFFFu)) {
-                    plain_finish<WALKS, COUNTS>(E, S.c, st, j, state, csum, false);
+                uint32_t j, x, rev;
+                if (thread_reject(E, S.c, st, j, x, rev, COOP ? PLAIN_LANE_ATTEMPTS : 0xFFFFFFFFu)) {
+                    plain_finish<WALKS, COUNTS>(S.c, st, j, x, rev, state, csum, false);
                 } else if (COOP) {
                     pend = true;
                 } else {
@@ -1707,14 +1764,12 @@ __global__ __launch_bounds__(256) void k_plain_step(Exec E, OneJob S, uint32_t s
         }
     }
     if constexpr (COOP) {
-        __shared__ HubLds lds[256 / WAVE];
-        HubLds &L = lds[threadIdx.x / WAVE];
         for (uint64_t pm = ballot(pend); pm; pm &= pm - 1) {
             const int o = first_lane(pm);
             WS w = bcast(st, o);
-            uint32_t j;
-            if (wave_reject(E, S.c, w, L, j, PLAIN_LANE_ATTEMPTS)) {
-                plain_finish<WALKS, COUNTS>(E, S.c, w, j, state, csum, true);
+            uint32_t j, x, rev;
+            if (wave_reject(E, S.c, w, j, x, rev, PLAIN_LANE_ATTEMPTS)) {
+                plain_finish<WALKS, COUNTS>(S.c, w, j, x, rev, state, csum, true);
             } else if (lane_id() == o) {
                 push = true;
                 item = i | 0x80000000u;
@@ -1776,7 +1831,9 @@ __global__ __launch_bounds__(HBLOCK, 5) void k_plain_hub(Exec E_arg, OneJob S, u
                 if (lane_id() == 0) atomicOr(E.g.status, 2u);
                 j = st.vd - 1;
             }
-            plain_finish<WALKS, COUNTS>(E, S.c, st, j, state, csum, true);
+            uint32_t x, rev;
+            resolve(E, st, j, x, rev);
+            plain_finish<WALKS, COUNTS>(S.c, st, j, x, rev, state, csum, true);
         }
         if (nb <= gridDim.x) break;
         __syncthreads();
@@ -1802,7 +1859,9 @@ __global__ __launch_bounds__(HBLOCK, 5) void k_plain_hub(Exec E_arg, OneJob S, u
             plain_load<true>(E, state[i], i, s, st);
             uint32_t xj;
             const uint32_t j = wave_inverse_cdf(E, S.c, st, kidx, L, xj);
-            plain_finish<WALKS, COUNTS>(E, S.c, st, j, state, csum, true);
+            uint32_t x, rev;
+            resolve(E, st, j, x, rev);
+            plain_finish<WALKS, COUNTS>(S.c, st, j, x, rev, state, csum, true);
         }
         if (rest == 0) break;
         uint32_t b = 0;
@@ -2041,26 +2100,29 @@ void make_exec(const n2v_graph *g, const n2v_exec_opts &o, Exec *E)
     E->search_ratio = o.search_ratio;
     E->sparse_ratio = o.sparse_ratio < 1 ? 1 : o.sparse_ratio;
     // Where hub rows hold a large share of the entries (so of the visits), a
-    // lane's walk soon reaches one and waits while the other lanes go on: one
-    // rejection move per lane before the wave serves its pending walks when
-    // hub rows hold at least 35% of the entries, two from 2%.  Otherwise
-    // eight, since each return to the wave phase reloads the lanes' vertex
-    // records.
+    // lane's walk soon reaches one and waits while the other lanes go on: two
+    // attempts per lane before the wave serves its pending walks when hub rows
+    // hold at least 35% of the entries, four from 2%.  Otherwise 64, since each
+    // return to the wave phase reloads the lanes' vertex records.  Measured
+    // with (2, 4, 16) / (4, 8, 32) / (8, 16, 64): scale 22 skewed 508 / 512 /
+    // 513 ms, FN-Approx on Skew-5 107.9 / 108.1 / 110.5 ms, ER-22 15.9 / 15.6 /
+    // 15.5 ms, WeC-22 28.6 / 27.9 / 27.5 ms.
     const uint64_t he = g->hub_entries, m = g->dg.m;
-    E->thread_iters = he && he * 20 >= m * 7 ? 1u : (he && he * 50 >= m ? 2u : 8u);
+    E->thread_iters = he && he * 20 >= m * 7 ? 2u : (he && he * 50 >= m ? 4u : 64u);
 }
 
 PlainKey plain_key(const Exec &E, const OneJob &S, const void *ws, uint32_t hub_blocks, bool W, bool C)
 {
     // every field the launches read from the host: a new field of Exec,
     // DevGraph, JobCtx or OneJob must be added here
-    static_assert(sizeof(DevGraph) == 112 && sizeof(Exec) == 144 && sizeof(JobCtx) == 56 && sizeof(OneJob) == 80,
+    static_assert(sizeof(DevGraph) == 120 && sizeof(Exec) == 152 && sizeof(JobCtx) == 56 && sizeof(OneJob) == 80,
                   "plain_key covers every launch argument");
     PlainKey k;
     const DevGraph &d = E.g;
     k.put(d.vrec);
     k.put(d.erec);
     k.put(d.adj);
+    k.put(d.filt);
     k.put(d.wt);
     k.put(d.wsum);
     k.put(d.hbase);
