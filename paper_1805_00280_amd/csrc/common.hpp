@@ -68,9 +68,24 @@ struct alignas(16) VRec {
     uint32_t wmax;
 };
 
+// Entries may carry their neighbour's row, so that an accepted move knows the
+// next row without reading its vertex record: one random line and one
+// dependent read less per move, against entries twice as long.  That pays on
+// large graphs of short rows without hubs (ER-22: 15.4 -> 11.2 ms), whose
+// vertex records are not in L2 and whose entries are no longer than that; it
+// gives 3% at mean degree 100 (WeC-22) and costs 8% where hub rows, whose
+// vertex records are hot, take many of the moves (FN-Approx on Skew-5).
+// Weighted moves need the record's largest weight in any case.  The share of
+// the hub rows is known only when the graph is created.
+__host__ __device__ inline bool wide_entries(uint64_t n, uint64_t m, bool weighted)
+{
+    return !weighted && n >= 1u << 18 && m <= 32 * n && m <= 1ull << 31;
+}
+
 struct DevGraph {
     const VRec *vrec;      // n
-    const uint2 *erec;     // m: (neighbour x, position of the reverse entry in N(x) or SENT)
+    const uint2 *erec;     // m: (neighbour x, position of the reverse entry in N(x) or SENT); null with nrec
+    const uint4 *nrec;     // m: the same and x's row (offset, degree); null with erec
     const uint32_t *adj;   // m, rows strictly ascending
     const uint64_t *filt;  // membership filter of every row (see filter_word), or null
     const uint16_t *wt;    // m, or null for an unweighted graph

@@ -205,15 +205,21 @@ __global__ __launch_bounds__(256) void k_vrec_w(const uint64_t *__restrict__ off
 }
 
 // Entry records, reverse positions still unknown (SENT), and the rows'
-// membership filters (cleared before; null: none).
+// membership filters (cleared before; null: none).  WIDE: nrec, else erec.
+template <bool WIDE>
 __global__ __launch_bounds__(256) void k_entries(const uint64_t *__restrict__ off, const uint32_t *__restrict__ adj,
-                                                 uint32_t n, uint64_t m, uint2 *__restrict__ erec,
+                                                 uint32_t n, uint64_t m, void *__restrict__ rec,
                                                  unsigned long long *__restrict__ filt)
 {
     each_entry(off, n, m, [&](uint64_t e, uint32_t v, bool, bool live) {
         if (!live) return;
         const uint32_t x = adj[e];
-        erec[e] = make_uint2(x, SENT);
+        if (WIDE) {
+            const uint64_t xlo = off[x];
+            ((uint4 *)rec)[e] = make_uint4(x, SENT, (uint32_t)xlo, (uint32_t)(off[x + 1] - xlo));
+        } else {
+            ((uint2 *)rec)[e] = make_uint2(x, SENT);
+        }
         if (filt) {
             const uint64_t lo = off[v];
             atomicOr(filt + filter_word(lo, (uint32_t)(off[v + 1] - lo), x), (unsigned long long)filter_bits(x));
@@ -226,21 +232,34 @@ __global__ __launch_bounds__(256) void k_entries(const uint64_t *__restrict__ of
 // and writes both positions: half the searches, none of them in a hub's row
 // from a leaf.  Bound by the random lines of the searches and of the partners'
 // 4-byte writes.  Counts the entries that found a partner.
+template <bool WIDE>
 __global__ __launch_bounds__(256) void k_reverse(const uint64_t *__restrict__ off, const uint32_t *__restrict__ adj,
-                                                 uint32_t n, uint64_t m, uint2 *__restrict__ erec,
+                                                 uint32_t n, uint64_t m, void *__restrict__ rec,
                                                  unsigned long long *__restrict__ paired)
 {
     uint64_t found = 0;
     each_entry(off, n, m, [&](uint64_t e, uint32_t v, bool, bool live) {
         if (!live) return;
-        const uint32_t x = adj[e];
-        const uint64_t vlo = off[v], xlo = off[x], xhi = off[x + 1];
-        const uint64_t dv = off[v + 1] - vlo, dx = xhi - xlo;
+        uint32_t x;
+        uint64_t xlo, dx;
+        if (WIDE) {
+            const uint4 r = ((const uint4 *)rec)[e];
+            x = r.x;
+            xlo = r.z;
+            dx = r.w;
+        } else {
+            x = adj[e];
+            xlo = off[x];
+            dx = off[x + 1] - xlo;
+        }
+        const uint64_t vlo = off[v], xhi = xlo + dx;
+        const uint64_t dv = off[v + 1] - vlo;
         if (dx < dv || (dx == dv && x < v)) {
             const uint64_t p = lower_bound_g(adj, xlo, xhi, v);
             if (p < xhi && adj[p] == v) {
-                erec[e].y = (uint32_t)(p - xlo);
-                erec[p].y = (uint32_t)(e - vlo);
+                uint32_t *w = (uint32_t *)rec;
+                w[e * (WIDE ? 4 : 2) + 1] = (uint32_t)(p - xlo);
+                w[p * (WIDE ? 4 : 2) + 1] = (uint32_t)(e - vlo);
                 found += 2;
             }
         }
@@ -342,7 +361,8 @@ __global__ void k_zero_u32(uint32_t *p, uint32_t n)
 
 struct GraphLayout {
     VRec *vrec;
-    uint2 *erec;
+    void *rec;  // entry records: uint4 where `wide`, and hub rows turn out few, else uint2
+    bool wide;
     uint64_t *filt;
     uint64_t *wsum;
     uint64_t *hbase;
@@ -358,7 +378,8 @@ size_t graph_layout(uint32_t n, uint64_t m, int weighted, void *ws, size_t ws_by
     L->status = c.take<uint32_t>(64);
     L->cursors = c.take<uint32_t>((uint64_t)CURSOR_SLOTS * CURSOR_STRIDE);
     L->vrec = c.take<VRec>((uint64_t)n + 1);
-    L->erec = c.take<uint2>(m ? m : 1);
+    L->wide = wide_entries(n, m, weighted);
+    L->rec = L->wide ? (void *)c.take<uint4>(m ? m : 1) : (void *)c.take<uint2>(m ? m : 1);
     L->filt = m <= FILTER_MAX_ENTRIES ? c.take<uint64_t>(filter_words(m)) : nullptr;
     L->wsum = weighted ? c.take<uint64_t>((uint64_t)n + 1) : nullptr;
     L->hbase = c.take<uint64_t>((uint64_t)n + 1);
@@ -453,10 +474,22 @@ extern "C" int n2v_graph_create(const uint64_t *off, const uint32_t *adj, const 
     if (L.filt)
         hipLaunchKernelGGL(k_fill0_u64, dim3(grid_for_threads(filter_words(m))), dim3(256), 0, st, L.filt,
                            filter_words(m));
-    hipLaunchKernelGGL(k_entries, dim3(grid_for_entries(m)), dim3(256), 0, st, off, adj, n, m, L.erec,
-                       (unsigned long long *)L.filt);
-    hipLaunchKernelGGL(k_zero_u64w, dim3(1), dim3(64), 0, st, L.hist, 1u);
-    hipLaunchKernelGGL(k_reverse, dim3(grid_for_entries(m)), dim3(256), 0, st, off, adj, n, m, L.erec, L.hist);
+    // entries in hub rows: they decide the kind of entry records here and the
+    // walk kernels' attempts per phase later
+    const uint64_t memo_min = (uint64_t)o.d_rule + 1;
+    unsigned long long hub_entries = 0;
+    hipLaunchKernelGGL(k_zero_u64w, dim3(1), dim3(64), 0, st, L.hist, 2u);
+    hipLaunchKernelGGL(k_deg_entries_ge, dim3(grid_for_waves(n)), dim3(256), 0, st, off, n, memo_min, L.hist + 1);
+    bool wide = L.wide;
+    if (wide) {
+        N2V_HIP(hipMemcpyAsync(&hub_entries, L.hist + 1, sizeof(hub_entries), hipMemcpyDeviceToHost, st));
+        N2V_HIP(hipStreamSynchronize(st));
+        wide = hub_entries * 50 < m;
+    }
+    hipLaunchKernelGGL(wide ? k_entries<true> : k_entries<false>, dim3(grid_for_entries(m)), dim3(256), 0, st, off,
+                       adj, n, m, L.rec, (unsigned long long *)L.filt);
+    hipLaunchKernelGGL(wide ? k_reverse<true> : k_reverse<false>, dim3(grid_for_entries(m)), dim3(256), 0, st, off,
+                       adj, n, m, L.rec, L.hist);
     N2V_HIP(hipGetLastError());
     if (o.validate >= 2) {
         unsigned long long paired = 0;
@@ -465,19 +498,14 @@ extern "C" int n2v_graph_create(const uint64_t *off, const uint32_t *adj, const 
         if (paired != m)
             return set_error(N2V_EGRAPH, "n2v_graph_create: CSR is not symmetric (flags 0x%x)", (unsigned)BAD_ASYM);
     }
-    const uint64_t memo_min = (uint64_t)o.d_rule + 1;
     hipLaunchKernelGGL(k_hub_len, dim3(grid_for_waves(n)), dim3(256), 0, st, off, n, memo_min, wt != nullptr,
                        L.hbase);
     N2V_HIP(hipGetLastError());
     int rc = exclusive_scan_u64(L.hbase, (uint64_t)n + 1, L.scan, st);
     if (rc) return rc;
     uint64_t hub_words = 0;
-    unsigned long long hub_entries = 0;
     uint32_t wrange[2] = {0, 0};
-    hipLaunchKernelGGL(k_zero_u64w, dim3(1), dim3(64), 0, st, L.hist, 1u);
-    hipLaunchKernelGGL(k_deg_entries_ge, dim3(grid_for_waves(n)), dim3(256), 0, st, off, n, memo_min, L.hist);
-    N2V_HIP(hipGetLastError());
-    N2V_HIP(hipMemcpyAsync(&hub_entries, L.hist, sizeof(hub_entries), hipMemcpyDeviceToHost, st));
+    N2V_HIP(hipMemcpyAsync(&hub_entries, L.hist + 1, sizeof(hub_entries), hipMemcpyDeviceToHost, st));
     N2V_HIP(hipMemcpyAsync(&hub_words, L.hbase + n, sizeof(uint64_t), hipMemcpyDeviceToHost, st));
     N2V_HIP(hipMemcpyAsync(wrange, L.status + 2, sizeof(wrange), hipMemcpyDeviceToHost, st));
     N2V_HIP(hipStreamSynchronize(st));
@@ -498,7 +526,8 @@ extern "C" int n2v_graph_create(const uint64_t *off, const uint32_t *adj, const 
     g->scan = L.scan;
     g->memo_bytes = 0;
     g->dg.vrec = L.vrec;
-    g->dg.erec = L.erec;
+    g->dg.erec = wide ? nullptr : (const uint2 *)L.rec;
+    g->dg.nrec = wide ? (const uint4 *)L.rec : nullptr;
     g->dg.adj = adj;
     g->dg.filt = L.filt;
     g->dg.wt = wt;

@@ -203,28 +203,62 @@ __device__ __forceinline__ void load_v(const Exec &E, WS &st, uint32_t x)
     st.vw = r.wmax;
 }
 
-// Neighbour index j of v -> (x, position of v in N(x)).
-__device__ __forceinline__ void resolve(const Exec &E, const WS &st, uint32_t j, uint32_t &x, uint32_t &rev)
+// A neighbour x of v: the position of v in N(x) and, with wide entry records,
+// x's row.
+struct Nb {
+    uint32_t x, rev, off, deg;
+};
+
+// Entry e of the graph.
+__device__ __forceinline__ Nb entry(const Exec &E, uint64_t e)
+{
+    Nb b;
+    if (E.g.nrec) {
+        const uint4 r = E.g.nrec[e];
+        b.x = r.x;
+        b.rev = r.y;
+        b.off = r.z;
+        b.deg = r.w;
+    } else {
+        const uint2 r = E.g.erec[e];
+        b.x = r.x;
+        b.rev = r.y;
+        b.off = b.deg = 0;
+    }
+    return b;
+}
+
+// Neighbour index j of v.
+__device__ __forceinline__ Nb resolve(const Exec &E, const WS &st, uint32_t j)
 {
     if (st.s > 0 && j == st.pos_t) {
-        x = st.t;
-        rev = st.jprev;
-    } else {
-        const uint2 e = E.g.erec[st.vo + j];
-        x = e.x;
-        rev = e.y;
+        Nb b;
+        b.x = st.t;
+        b.rev = st.jprev;
+        b.off = (uint32_t)st.to;
+        b.deg = st.td;
+        return b;
     }
+    return entry(E, st.vo + j);
 }
 
 template <bool HUB = false>
-__device__ __forceinline__ void advance(const Exec &E, WS &st, uint32_t j, uint32_t x, uint32_t rev)
+__device__ __forceinline__ void advance(const Exec &E, WS &st, uint32_t j, const Nb &b)
 {
     st.t = st.v;
     st.to = st.vo;
     st.td = st.vd;
     st.jprev = j;
-    st.pos_t = rev;
-    load_v<HUB>(E, st, x);
+    st.pos_t = b.rev;
+    if (E.g.nrec) {
+        st.v = b.x;
+        st.vo = b.off;
+        st.vd = b.deg;
+        st.vw = 1;  // unweighted; not read at a dead end
+        st.hb = HUB && E.g.memo ? E.g.hbase[b.x] : ~0ull;
+    } else {
+        load_v<HUB>(E, st, b.x);
+    }
     st.s += 1;
 }
 
@@ -279,47 +313,50 @@ __device__ __forceinline__ bool is_member(const Exec &E, const WS &st, uint32_t 
 }
 
 // One rejection attempt k; returns whether it accepts, its neighbour index,
-// and, accepted, that neighbour and the position of v in its row.  The entry
+// and, accepted, that neighbour.  The entry
 // record that the test reads for x serves the accepted move too.
 __device__ __forceinline__ bool attempt(const Exec &E, const JobCtx &J, const WS &st, uint32_t k, uint32_t &j_out,
-                                        uint32_t &x, uint32_t &rev)
+                                        Nb &b)
 {
     Att a;
     const int r = attempt_pre(E, J, st, k, a);
     j_out = a.j;
     if (r == 0) return false;
-    resolve(E, st, a.j, x, rev);
+    b = resolve(E, st, a.j);
     if (r == 1) return true;
-    return a.u < (is_member(E, st, x) ? A_COM : J.A_out) * a.w;
+    return a.u < (is_member(E, st, b.x) ? A_COM : J.A_out) * a.w;
 }
 
 // Thread class: attempts in order until one accepts (false after a_cap, or
 // after the first kmax attempts).
-__device__ bool thread_reject(const Exec &E, const JobCtx &J, const WS &st, uint32_t &j_out, uint32_t &x,
-                              uint32_t &rev, uint32_t kmax = 0xFFFFFFFFu)
+__device__ bool thread_reject(const Exec &E, const JobCtx &J, const WS &st, uint32_t &j_out, Nb &b,
+                              uint32_t kmax = 0xFFFFFFFFu)
 {
     const uint32_t n = kmax < E.g.a_cap ? kmax : E.g.a_cap;
     for (uint32_t k = 0; k < n; ++k)
-        if (attempt(E, J, st, k, j_out, x, rev)) return true;
+        if (attempt(E, J, st, k, j_out, b)) return true;
     return false;
 }
 
 // Wave class: lanes take attempts k0 + lane (from attempt kfrom on, the
 // earlier ones having rejected); the lowest accepting one wins.
-__device__ bool wave_reject(const Exec &E, const JobCtx &J, const WS &st_in, uint32_t &j_out, uint32_t &x_out,
-                            uint32_t &rev_out, uint32_t kfrom = 0)
+__device__ bool wave_reject(const Exec &E, const JobCtx &J, const WS &st_in, uint32_t &j_out, Nb &b_out,
+                            uint32_t kfrom = 0)
 {
     const WS st = uniform_ws(st_in);
     for (uint32_t k0 = kfrom; k0 < E.g.a_cap; k0 += WAVE) {
         const uint32_t k = k0 + lane_id();
-        uint32_t j = 0, x = 0, rev = 0;
-        const bool acc = k < E.g.a_cap && attempt(E, J, st, k, j, x, rev);
+        uint32_t j = 0;
+        Nb b = {};
+        const bool acc = k < E.g.a_cap && attempt(E, J, st, k, j, b);
         const uint64_t m = ballot(acc);
         if (m) {
             const int f = first_lane(m);
             j_out = lane_val(j, f);
-            x_out = lane_val(x, f);
-            rev_out = lane_val(rev, f);
+            b_out.x = lane_val(b.x, f);
+            b_out.rev = lane_val(b.rev, f);
+            b_out.off = lane_val(b.off, f);
+            b_out.deg = lane_val(b.deg, f);
             return true;
         }
     }
@@ -1475,24 +1512,29 @@ __device__ __forceinline__ void ws_to_slot(const WS &st, uint32_t flags, uint32_
     q.flags = flags | (st.job << SL_JOB);
 }
 
-// The graph view a kernel instantiated for unweighted graphs (WT false)
-// works with: a null weight array the compiler can see, so the weighted
-// branches of every move drop out of its code (and its registers).
-template <bool WT>
+// What kind of graph a kernel is instantiated for: null arrays the compiler can
+// see, so the branches of the other kinds drop out of its code (and its
+// registers).
+enum Kind { PLAIN_ENTRIES, WIDE_ENTRIES, WEIGHTED };
+
+__host__ inline Kind kind_of(const Exec &E) { return E.g.wt ? WEIGHTED : (E.g.nrec ? WIDE_ENTRIES : PLAIN_ENTRIES); }
+
+template <Kind K>
 __device__ __forceinline__ Exec exec_for(const Exec &E)
 {
     Exec e = E;
-    if (!WT) {
+    if (K != WEIGHTED) {
         e.g.wt = nullptr;
         e.g.wsum = nullptr;
     }
+    if (K != WIDE_ENTRIES) e.g.nrec = nullptr;
     return e;
 }
 
-template <class Src, bool WALKS, bool COUNTS, bool WT>
+template <class Src, bool WALKS, bool COUNTS, Kind K>
 __global__ __launch_bounds__(PBLOCK, 5) void k_persistent(Exec E_arg, Src S)
 {
-    const Exec E = exec_for<WT>(E_arg);
+    const Exec E = exec_for<K>(E_arg);
     __shared__ HubLds lds[PBLOCK / WAVE];
     __shared__ Slot slots[PBLOCK / WAVE][WAVE];
     HubLds &L = lds[threadIdx.x / WAVE];
@@ -1576,10 +1618,11 @@ __global__ __launch_bounds__(PBLOCK, 5) void k_persistent(Exec E_arg, Src S)
                 // soon as some lane waits for either
                 if (it >= E.thread_iters && act != ~0ull && (!exhausted || ballot(pend))) break;
                 if (!can) continue;
-                uint32_t j, x, rev;
-                if (attempt(E, J, st, k, j, x, rev)) {
-                    put<WALKS, COUNTS>(J, st.i, st.s + 1, x, cb, csum);
-                    advance(E, st, j, x, rev);
+                uint32_t j;
+                Nb b;
+                if (attempt(E, J, st, k, j, b)) {
+                    put<WALKS, COUNTS>(J, st.i, st.s + 1, b.x, cb, csum);
+                    advance(E, st, j, b);
                     k = 0;
                     if (st.s == J.L || st.vd == 0) {
                         flush<WALKS>(J, st.i, st.s, cb);
@@ -1620,28 +1663,29 @@ __global__ __launch_bounds__(PBLOCK, 5) void k_persistent(Exec E_arg, Src S)
             bool capped = q.flags & SL_CAP;
             bool alive = true;
             for (;;) {
-                uint32_t j = 0, x, rev, kidx = capped ? E.g.a_cap : 0u;
+                uint32_t j = 0, kidx = capped ? E.g.a_cap : 0u;
+                Nb b;
                 bool icdf = capped || w.vd > E.g.d_rule;
-                if (!icdf && !wave_reject(E, J, w, j, x, rev)) {
+                if (!icdf && !wave_reject(E, J, w, j, b)) {
                     icdf = true;
                     kidx = E.g.a_cap;
                 }
-                uint32_t xj = SENT;
-                if (icdf) j = wave_inverse_cdf(E, J, w, kidx, L, xj);
-                if (!icdf) {
-                    // the accepting lane's entry is known
-                } else if (xj != SENT && !(w.s > 0 && j == w.pos_t)) {
-                    // the neighbour is known: its record and the reverse
-                    // position load together
-                    x = xj;
-                    rev = E.g.erec[w.vo + j].y;
-                } else {
-                    resolve(E, w, j, x, rev);
+                if (icdf) {
+                    uint32_t xj = SENT;
+                    j = wave_inverse_cdf(E, J, w, kidx, L, xj);
+                    if (xj != SENT && j != w.pos_t && !E.g.nrec) {
+                        // the neighbour is known: its record and the reverse
+                        // position load together
+                        b.x = xj;
+                        b.rev = E.g.erec[w.vo + j].y;
+                    } else {
+                        b = resolve(E, w, j);
+                    }
                 }
-                x = uni(x);
-                rev = uni(rev);
-                if (l == 0) emit<WALKS, COUNTS>(J, w.i, w.s + 1, x, csum);
-                advance<true>(E, w, j, x, rev);
+                b.x = uni(b.x);
+                b.rev = uni(b.rev);
+                if (l == 0) emit<WALKS, COUNTS>(J, w.i, w.s + 1, b.x, csum);
+                advance<true>(E, w, j, b);
                 w = uniform_ws(w);
                 capped = false;
                 if (w.s == J.L || w.vd == 0) {
@@ -1708,14 +1752,14 @@ __device__ __forceinline__ bool plain_load(const Exec &E, const uint4 &q, uint32
 }
 
 template <bool WALKS, bool COUNTS>
-__device__ __forceinline__ void plain_finish(const JobCtx &J, WS &st, uint32_t j, uint32_t x, uint32_t rev,
-                                             uint4 *state, uint64_t &csum, bool wave)
+__device__ __forceinline__ void plain_finish(const JobCtx &J, WS &st, uint32_t j, const Nb &b, uint4 *state,
+                                             uint64_t &csum, bool wave)
 {
-    if (!wave || lane_id() == 0) emit<WALKS, COUNTS>(J, st.i, st.s + 1, x, csum);
+    if (!wave || lane_id() == 0) emit<WALKS, COUNTS>(J, st.i, st.s + 1, b.x, csum);
     // a dead end at x is found by the next superstep, which loads x's record
     // anyway
     const bool end = st.s + 1 == J.L;
-    if (!wave || lane_id() == 0) state[st.i] = make_uint4(end ? SENT : x, st.v, rev, j);
+    if (!wave || lane_id() == 0) state[st.i] = make_uint4(end ? SENT : b.x, st.v, b.rev, j);
 }
 
 // Rejection attempts a lane of the plain thread kernel makes alone when a
@@ -1726,11 +1770,12 @@ constexpr uint32_t PLAIN_LANE_ATTEMPTS = 16;
 
 // Hub moves are queued for k_plain_hub: dense moves at degree > t_wg at the
 // top of hubq (growing down, one workgroup each), all others at the bottom.
-template <bool WALKS, bool COUNTS, bool COOP>
-__global__ __launch_bounds__(256) void k_plain_step(Exec E, OneJob S, uint32_t s, uint4 *__restrict__ state,
+template <bool WALKS, bool COUNTS, Kind K, bool COOP>
+__global__ __launch_bounds__(256) void k_plain_step(Exec E_arg, OneJob S, uint32_t s, uint4 *__restrict__ state,
                                                     uint32_t *__restrict__ hubq, uint32_t *__restrict__ hubn,
                                                     uint32_t *__restrict__ bign)
 {
+    const Exec E = exec_for<K>(E_arg);
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     uint64_t csum = 0;
     bool push = false, big = false, pend = false;
@@ -1751,9 +1796,10 @@ __global__ __launch_bounds__(256) void k_plain_step(Exec E, OneJob S, uint32_t s
                         st.vd <= MEMO_MAX_DEG && sketch_row(E, st, st.pos_t)[0] != 0);
                 push = !big;
             } else {
-                uint32_t j, x, rev;
-                if (thread_reject(E, S.c, st, j, x, rev, COOP ? PLAIN_LANE_ATTEMPTS : 0xFFFFFFFFu)) {
-                    plain_finish<WALKS, COUNTS>(S.c, st, j, x, rev, state, csum, false);
+                uint32_t j;
+                Nb b;
+                if (thread_reject(E, S.c, st, j, b, COOP ? PLAIN_LANE_ATTEMPTS : 0xFFFFFFFFu)) {
+                    plain_finish<WALKS, COUNTS>(S.c, st, j, b, state, csum, false);
                 } else if (COOP) {
                     pend = true;
                 } else {
@@ -1767,9 +1813,10 @@ __global__ __launch_bounds__(256) void k_plain_step(Exec E, OneJob S, uint32_t s
         for (uint64_t pm = ballot(pend); pm; pm &= pm - 1) {
             const int o = first_lane(pm);
             WS w = bcast(st, o);
-            uint32_t j, x, rev;
-            if (wave_reject(E, S.c, w, j, x, rev, PLAIN_LANE_ATTEMPTS)) {
-                plain_finish<WALKS, COUNTS>(S.c, w, j, x, rev, state, csum, true);
+            uint32_t j;
+            Nb b;
+            if (wave_reject(E, S.c, w, j, b, PLAIN_LANE_ATTEMPTS)) {
+                plain_finish<WALKS, COUNTS>(S.c, w, j, b, state, csum, true);
             } else if (lane_id() == o) {
                 push = true;
                 item = i | 0x80000000u;
@@ -1801,13 +1848,13 @@ __global__ __launch_bounds__(256) void k_plain_step(Exec E, OneJob S, uint32_t s
 // The hub moves of this superstep: first the large dense ones, one workgroup
 // each (largest work first shortens the superstep's tail), then the rest,
 // one wavefront each.
-template <bool WALKS, bool COUNTS, bool WT>
+template <bool WALKS, bool COUNTS, Kind K>
 __global__ __launch_bounds__(HBLOCK, 5) void k_plain_hub(Exec E_arg, OneJob S, uint32_t s, uint4 *__restrict__ state,
                                                          const uint32_t *__restrict__ hubq,
                                                          const uint32_t *__restrict__ hubn, uint32_t *__restrict__ hubd,
                                                          const uint32_t *__restrict__ bign, uint32_t *__restrict__ bigd)
 {
-    const Exec E = exec_for<WT>(E_arg);
+    const Exec E = exec_for<K>(E_arg);
     __shared__ HubLds lds[HBLOCK / WAVE];
     __shared__ BlkLds blk;
     HubLds &L = lds[threadIdx.x / WAVE];
@@ -1831,9 +1878,7 @@ __global__ __launch_bounds__(HBLOCK, 5) void k_plain_hub(Exec E_arg, OneJob S, u
                 if (lane_id() == 0) atomicOr(E.g.status, 2u);
                 j = st.vd - 1;
             }
-            uint32_t x, rev;
-            resolve(E, st, j, x, rev);
-            plain_finish<WALKS, COUNTS>(S.c, st, j, x, rev, state, csum, true);
+            plain_finish<WALKS, COUNTS>(S.c, st, j, resolve(E, st, j), state, csum, true);
         }
         if (nb <= gridDim.x) break;
         __syncthreads();
@@ -1859,9 +1904,7 @@ __global__ __launch_bounds__(HBLOCK, 5) void k_plain_hub(Exec E_arg, OneJob S, u
             plain_load<true>(E, state[i], i, s, st);
             uint32_t xj;
             const uint32_t j = wave_inverse_cdf(E, S.c, st, kidx, L, xj);
-            uint32_t x, rev;
-            resolve(E, st, j, x, rev);
-            plain_finish<WALKS, COUNTS>(S.c, st, j, x, rev, state, csum, true);
+            plain_finish<WALKS, COUNTS>(S.c, st, j, resolve(E, st, j), state, csum, true);
         }
         if (rest == 0) break;
         uint32_t b = 0;
@@ -1901,7 +1944,7 @@ DevInfo &dev_info(int dev)
         if (hipGetDeviceProperties(&prop, dev) == hipSuccess) d.cus = prop.multiProcessorCount;
         if (d.cus <= 0) d.cus = 256;
         int b = 0;
-        (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, (const void *)k_persistent<OneJob, true, true, true>,
+        (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, (const void *)k_persistent<OneJob, true, true, WEIGHTED>,
                                                            PBLOCK, 0);
         d.occ = b > 0 ? b : 2;
     }
@@ -1934,18 +1977,17 @@ template <bool W, bool C>
 int launch_persistent(const Exec &E, const OneJob &S, const n2v_exec_opts &o, int dev, hipStream_t st)
 {
     hipLaunchKernelGGL(k_zero, dim3(1), dim3(64), 0, st, S.cur, 1u);
-    if (E.g.wt)
-        hipLaunchKernelGGL((k_persistent<OneJob, W, C, true>), dim3(persistent_blocks(o, dev, S.n)), dim3(PBLOCK), 0,
-                           st, E, S);
-    else
-        hipLaunchKernelGGL((k_persistent<OneJob, W, C, false>), dim3(persistent_blocks(o, dev, S.n)), dim3(PBLOCK), 0,
-                           st, E, S);
+    const Kind K = kind_of(E);
+    auto kernel = K == WEIGHTED       ? k_persistent<OneJob, W, C, WEIGHTED>
+                  : K == WIDE_ENTRIES ? k_persistent<OneJob, W, C, WIDE_ENTRIES>
+                                      : k_persistent<OneJob, W, C, PLAIN_ENTRIES>;
+    hipLaunchKernelGGL(kernel, dim3(persistent_blocks(o, dev, S.n)), dim3(PBLOCK), 0, st, E, S);
     N2V_HIP(hipGetLastError());
     return N2V_OK;
 }
 
-template <bool W, bool C>
-int launch_plain(const Exec &E, const OneJob &S, void *ws, int dev, hipStream_t st)
+template <bool W, bool C, Kind K>
+int launch_plain_kind(const Exec &E, const OneJob &S, void *ws, int dev, hipStream_t st)
 {
     Carver c(ws, (size_t)-1);
     uint4 *state = c.take<uint4>(S.n ? S.n : 1);
@@ -1969,20 +2011,25 @@ int launch_plain(const Exec &E, const OneJob &S, void *ws, int dev, hipStream_t 
     const uint32_t sblocks = (S.n + tpb - 1) / tpb;
     for (uint32_t s = 0; s < S.c.L; ++s) {
         if (tpb == 64)
-            hipLaunchKernelGGL((k_plain_step<W, C, true>), dim3(sblocks), dim3(tpb), 0, st, E, S, s, state, hubq,
+            hipLaunchKernelGGL((k_plain_step<W, C, K, true>), dim3(sblocks), dim3(tpb), 0, st, E, S, s, state, hubq,
                                hubn + s, bign + s);
         else
-            hipLaunchKernelGGL((k_plain_step<W, C, false>), dim3(sblocks), dim3(tpb), 0, st, E, S, s, state, hubq,
+            hipLaunchKernelGGL((k_plain_step<W, C, K, false>), dim3(sblocks), dim3(tpb), 0, st, E, S, s, state, hubq,
                                hubn + s, bign + s);
-        if (E.g.wt)
-            hipLaunchKernelGGL((k_plain_hub<W, C, true>), dim3(hub_blocks), dim3(HBLOCK), 0, st, E, S, s, state, hubq,
-                               (const uint32_t *)(hubn + s), hubd + s, (const uint32_t *)(bign + s), bigd + s);
-        else
-            hipLaunchKernelGGL((k_plain_hub<W, C, false>), dim3(hub_blocks), dim3(HBLOCK), 0, st, E, S, s, state,
-                               hubq, (const uint32_t *)(hubn + s), hubd + s, (const uint32_t *)(bign + s), bigd + s);
+        hipLaunchKernelGGL((k_plain_hub<W, C, K>), dim3(hub_blocks), dim3(HBLOCK), 0, st, E, S, s, state, hubq,
+                           (const uint32_t *)(hubn + s), hubd + s, (const uint32_t *)(bign + s), bigd + s);
     }
     N2V_HIP(hipGetLastError());
     return N2V_OK;
+}
+
+template <bool W, bool C>
+int launch_plain(const Exec &E, const OneJob &S, void *ws, int dev, hipStream_t st)
+{
+    const Kind K = kind_of(E);
+    if (K == WEIGHTED) return launch_plain_kind<W, C, WEIGHTED>(E, S, ws, dev, st);
+    if (K == WIDE_ENTRIES) return launch_plain_kind<W, C, WIDE_ENTRIES>(E, S, ws, dev, st);
+    return launch_plain_kind<W, C, PLAIN_ENTRIES>(E, S, ws, dev, st);
 }
 
 }  // namespace
@@ -2115,12 +2162,13 @@ PlainKey plain_key(const Exec &E, const OneJob &S, const void *ws, uint32_t hub_
 {
     // every field the launches read from the host: a new field of Exec,
     // DevGraph, JobCtx or OneJob must be added here
-    static_assert(sizeof(DevGraph) == 120 && sizeof(Exec) == 152 && sizeof(JobCtx) == 56 && sizeof(OneJob) == 80,
+    static_assert(sizeof(DevGraph) == 128 && sizeof(Exec) == 160 && sizeof(JobCtx) == 56 && sizeof(OneJob) == 80,
                   "plain_key covers every launch argument");
     PlainKey k;
     const DevGraph &d = E.g;
     k.put(d.vrec);
     k.put(d.erec);
+    k.put(d.nrec);
     k.put(d.adj);
     k.put(d.filt);
     k.put(d.wt);
@@ -2237,10 +2285,11 @@ int launch_job_table(const Exec &E, const TableHdr *hdr, uint32_t blocks, hipStr
 {
     JobTable T;
     T.hdr = hdr;
-    if (E.g.wt)
-        hipLaunchKernelGGL((k_persistent<JobTable, true, false, true>), dim3(blocks), dim3(PBLOCK), 0, st, E, T);
-    else
-        hipLaunchKernelGGL((k_persistent<JobTable, true, false, false>), dim3(blocks), dim3(PBLOCK), 0, st, E, T);
+    const Kind K = kind_of(E);
+    auto kernel = K == WEIGHTED       ? k_persistent<JobTable, true, false, WEIGHTED>
+                  : K == WIDE_ENTRIES ? k_persistent<JobTable, true, false, WIDE_ENTRIES>
+                                      : k_persistent<JobTable, true, false, PLAIN_ENTRIES>;
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(PBLOCK), 0, st, E, T);
     N2V_HIP(hipGetLastError());
     return N2V_OK;
 }
