@@ -64,23 +64,19 @@ constexpr int NSUPER = MEMO_SEGS;   // segments (sums) per hub row
 constexpr int SPCAP = 1024;         // specials (positions) held by the sparse path
 constexpr int NPIV = 256;           // pivots of an N(t) range that N(v) entries are searched in
 
-// LDS of one wavefront for hub moves (5.5 KiB).
+// LDS of one wavefront for hub moves (5 KiB).
 struct HubLds {
     union {
         struct {
             uint32_t xs[TX];
             uint8_t flag[TX];
-            uint32_t rc[NSUPER];  // reverse sketch: members of N(v) per segment of N(t)
-            uint32_t rh[NSUPER];  // reverse sketch: encoded start hints
-            uint32_t r1[NSUPER];  // reverse sketch: members in each segment's first half
+            uint32_t hc[2 * NSUPER];  // reverse sketch: members of N(v) per half segment of N(t)
+            uint32_t rh[NSUPER];      // reverse sketch: encoded start hints
         } d;
         struct {
             uint32_t pos[SPCAP];
         } sp;
     } a;
-    union {
-        uint64_t csum[NSUPER];
-    } b;
     union {
         int32_t dl[HCH];     // weighted scan deltas, sparse sketch counts
         uint32_t piv[NPIV];  // pivots for searching N(v) entries in N(t)
@@ -377,37 +373,80 @@ __device__ __forceinline__ uint32_t hint_shift(uint32_t d)
 }
 
 // The sketch of the reverse pair (t, index of v in N(t)) that a merge of N(v)
-// with N(t) also yields: counts of common entries per segment of N(t) and,
-// for each segment's first entry, its lower bound in N(v) as a start hint.
+// with N(t) also yields: counts of common entries per half segment of N(t)
+// and, for each segment's first entry, its lower bound in N(v) as a start
+// hint.  N(t) is streamed in order, so the merge keeps the half segment it is
+// in and that half's count in scalars (64 entries cross at most one boundary,
+// halves being at least 256 long) and adds them to LDS where a half ends.
+// Dividing each entry's index by the segment length and adding every hit to
+// LDS took more instructions than the searches: with the scalars, and members
+// counted from ballots instead of flags, scale 22 skewed 507 -> 452 ms, visit
+// counts at scale 21 173 -> 162 ms, scale 18 without sketches 40.4 -> 37.2 ms.
 struct RevSketch {
-    uint32_t rseg;   // segment length of N(t); 0: not collected
+    uint32_t half;   // half the segment length of N(t); 0: not collected
     uint32_t nsp;    // entries per array of t's sketch row (memo_segs(deg t))
     uint32_t shift;  // hint_shift(deg v)
-    uint32_t *rc;    // LDS counts
-    uint32_t *rh;    // LDS encoded hints
-    uint32_t *r1;    // LDS counts in each segment's first half
+    uint32_t *hc;    // LDS counts per half segment (2 NSUPER)
+    uint32_t *rh;    // LDS encoded hints per segment
+    // the stream's state: the half it is in, where the next one begins, and
+    // the hits so far in this one
+    uint32_t at, next, acc;
+
+    // The stream begins at index y of N(t); an index on a boundary is still
+    // to cross it.
+    __device__ __forceinline__ void begin(uint32_t y)
+    {
+        if (!half) return;
+        const uint32_t h = (y + half - 1) / half;
+        next = uni(h * half);
+        at = uni(h) - 1u;  // 2^32 - 1 before the first half: nothing is counted there
+        acc = 0;
+    }
+
+    __device__ __forceinline__ void end()
+    {
+        if (half && acc && lane_id() == 0) atomicAdd(&hc[at], acc);
+        acc = 0;
+    }
+
+    // Lanes 0 .. nin-1 hold indices y0 + lane of N(t), M the hits among them,
+    // p the lane's lower bound in N(v).
+    __device__ __forceinline__ void count(uint32_t y0, uint32_t nin, uint64_t M, uint32_t p)
+    {
+        if (!half) return;
+        const uint32_t nb = next - y0;
+        if (nb < nin) {
+            const uint64_t before = M & ((1ull << nb) - 1ull);
+            acc += (uint32_t)__popcll(before);
+            if (acc && lane_id() == 0) atomicAdd(&hc[at], acc);
+            at += 1;
+            next += half;
+            acc = (uint32_t)__popcll(M ^ before);
+            if (!(at & 1u) && lane_id() == (int)nb) rh[at >> 1] = (p >> shift) + 1;
+        } else {
+            acc += (uint32_t)__popcll(M);
+        }
+    }
 };
 
-// Flags the tile entries equal to a block of NB x 64 entries of N(t) loaded
-// from ypos; returns how many block entries lie in the tile's value range
-// (they form a prefix of the block, N(t) being sorted).  The lower bounds in
-// the tile are found by branchless searches that advance SEARCH_ILP entries
-// per lane in lockstep, so their LDS reads overlap instead of each probe
-// waiting for the previous one.
+// Looks a block of NB x 64 entries of N(t), loaded from ypos (0xFFFFFFFF past
+// the end), up in the staged tile; returns how many lie in the tile's value
+// range (they form a prefix of the block, N(t) being sorted).  The lower
+// bounds in the tile are found by branchless searches that advance SEARCH_ILP
+// entries per lane in lockstep, so their LDS reads overlap instead of each
+// probe waiting for the previous one.  FLAGS marks the hits' tile entries;
+// without, c counts them, those among the tile's first 256 entries also in
+// its upper half.
 constexpr int SEARCH_ILP = 4;
 
-template <int NB>
-__device__ __forceinline__ uint32_t flag_block(HubLds &L, const uint32_t (&y)[NB], uint32_t ypos, uint32_t td,
-                                               uint32_t j0, uint32_t cnt, uint32_t xlast, const RevSketch &R)
+template <int NB, bool FLAGS>
+__device__ __forceinline__ uint32_t flag_block(HubLds &L, const uint32_t (&y)[NB], uint32_t ypos, uint32_t j0,
+                                               uint32_t xlast, RevSketch &R, uint32_t &c)
 {
     static_assert(NB % SEARCH_ILP == 0, "blocks are searched SEARCH_ILP entries per lane at a time");
-    const int l = lane_id();
     uint32_t nin = 0;
 #pragma unroll
-    for (int b = 0; b < NB; ++b) nin += __popcll(ballot(ypos + b * WAVE + l < td && y[b] <= xlast));
-#pragma unroll
     for (int g = 0; g < NB; g += SEARCH_ILP) {
-        if ((uint32_t)(g * WAVE) >= nin) break;  // the rest of the block lies beyond the tile
         // the probes walk LDS pointers, so each address is the pointer plus
         // an immediate offset
         const uint32_t *q[SEARCH_ILP];
@@ -418,36 +457,41 @@ __device__ __forceinline__ uint32_t flag_block(HubLds &L, const uint32_t (&y)[NB
 #pragma unroll
             for (int k = 0; k < SEARCH_ILP; ++k) q[k] += q[k][step - 1] < y[g + k] ? step : 0u;
         }
-        uint32_t pos[SEARCH_ILP];
+        uint32_t xq[SEARCH_ILP];
 #pragma unroll
-        for (int k = 0; k < SEARCH_ILP; ++k) pos[k] = (uint32_t)(q[k] - L.a.d.xs);
+        for (int k = 0; k < SEARCH_ILP; ++k) xq[k] = q[k][0];
 #pragma unroll
         for (int k = 0; k < SEARCH_ILP; ++k) {
-            const uint32_t idx = ypos + (g + k) * WAVE + l;
-            const bool in = idx < td && y[g + k] <= xlast;
-            const bool hit = in && pos[k] < cnt && L.a.d.xs[pos[k]] == y[g + k];
-            if (hit) L.a.d.flag[pos[k]] = 1;
-            if (R.rseg && in && (hit || (idx & (TX - 1)) == 0)) {
-                const uint32_t q = idx / R.rseg;
-                if (hit) {
-                    atomicAdd(&R.rc[q], 1u);
-                    if (idx - q * R.rseg < R.rseg / 2) atomicAdd(&R.r1[q], 1u);
-                }
-                if (idx == q * R.rseg) R.rh[q] = ((j0 + pos[k]) >> R.shift) + 1;
+            // entries past the tile's range, the padding among them, are out
+            const uint64_t in = ballot(y[g + k] <= xlast);
+            const bool hit = xq[k] == y[g + k] && y[g + k] <= xlast;
+            const uint32_t pos = (uint32_t)(q[k] - L.a.d.xs);
+            const uint64_t M = ballot(hit);
+            if (FLAGS) {
+                if (hit) L.a.d.flag[pos] = 1;
+            } else {
+                c += (uint32_t)__popcll(M) + ((uint32_t)__popcll(M & ballot(pos < (uint32_t)TX / 2)) << 16);
             }
+            R.count(ypos + (g + k) * WAVE, (uint32_t)__popcll(in), M, j0 + pos);
+            nin += (uint32_t)__popcll(in);
         }
+        if (nin < (uint32_t)((g + SEARCH_ILP) * WAVE)) break;  // the rest of the block lies beyond the tile
     }
     return nin;
 }
 
-// Stages N(v)[j0, j0+cnt) (cnt <= TX) in LDS and flags the members of N(t),
+// Stages N(v)[j0, j0+cnt) (cnt <= TX) in LDS and finds the members of N(t),
 // streaming N(t) from ypos (advanced past every value <= the tile's last
 // entry).  The tile and a first, small block of N(t) are loaded together
 // (most windows are short); a block consumed entirely is followed by
-// full-size blocks.  Returns the number of flagged entries, plus 2^16 times
-// the number among the tile's first 256 entries.
-__device__ uint32_t dense_flags(const uint32_t *__restrict__ X, const uint32_t *__restrict__ Y, uint32_t td,
-                                HubLds &L, uint32_t j0, uint32_t cnt, uint32_t &ypos, const RevSketch &R)
+// full-size blocks.  FLAGS leaves the members flagged (for locating an entry
+// or summing weights); a merge that only counts them does without the flags.
+// Returns the number of members, plus 2^16 times the number among the tile's
+// first 256 entries.
+template <bool FLAGS>
+__device__ __forceinline__ uint32_t dense_flags(const uint32_t *__restrict__ X, const uint32_t *__restrict__ Y,
+                                                uint32_t td, HubLds &L, uint32_t j0, uint32_t cnt, uint32_t &ypos,
+                                                RevSketch &R)
 {
     const int l = lane_id();
     uint32_t xv[XPL], y0[YFIRST];
@@ -463,10 +507,11 @@ __device__ uint32_t dense_flags(const uint32_t *__restrict__ X, const uint32_t *
     }
 #pragma unroll
     for (int e = 0; e < XPL; ++e) L.a.d.xs[e * WAVE + l] = xv[e];
-    *(uint64_t *)&L.a.d.flag[l * XPL] = 0;
+    if (FLAGS) *(uint64_t *)&L.a.d.flag[l * XPL] = 0;
     wave_lds_sync();
-    const uint32_t xlast = L.a.d.xs[cnt - 1];
-    uint32_t nin = flag_block<YFIRST>(L, y0, ypos, td, j0, cnt, xlast, R);
+    const uint32_t xlast = uni(L.a.d.xs[cnt - 1]);
+    uint32_t c = 0;
+    uint32_t nin = flag_block<YFIRST, FLAGS>(L, y0, ypos, j0, xlast, R, c);
     ypos += nin;
     if (nin == YFIRST * WAVE) {
         while (ypos < td) {
@@ -476,17 +521,18 @@ __device__ uint32_t dense_flags(const uint32_t *__restrict__ X, const uint32_t *
                 const uint32_t idx = ypos + b * WAVE + l;
                 y[b] = idx < td ? Y[idx] : 0xFFFFFFFFu;
             }
-            nin = flag_block<YPL>(L, y, ypos, td, j0, cnt, xlast, R);
+            nin = flag_block<YPL, FLAGS>(L, y, ypos, j0, xlast, R, c);
             ypos += nin;
             if (nin < YPL * WAVE) break;
         }
     }
     wave_lds_sync();
-    // flags are 0/1 bytes: the byte sum of the lane's eight; lanes 0..31 hold
+    if (!FLAGS) return c;
+    // flags are 0/1 bytes: the bit count of the lane's eight; lanes 0..31 hold
     // the tile's first 256 entries
     const uint64_t f8 = *(const uint64_t *)&L.a.d.flag[l * XPL];
-    const uint32_t c = (uint32_t)((f8 * 0x0101010101010101ull) >> 56);
-    return wave_sum32(l < WAVE / 2 ? c | (c << 16) : c);
+    const uint32_t n = (uint32_t)__popcll(f8);
+    return wave_sum32(l < WAVE / 2 ? n | (n << 16) : n);
 }
 
 // np (a power of two, 64..NPIV) pivots of Y[ylo, yhi) in LDS: bucket k is
@@ -536,7 +582,7 @@ __device__ __forceinline__ void pivot_buckets(const HubLds &L, uint32_t np, cons
 // search inside the bucket, SEARCH_ILP entries per lane at a time.  Returns
 // the number flagged (plus 2^16 times the number among the tile's first 256
 // entries); lb0 receives the lower bound in N(t) of the tile's first
-// entry.  Matches are also counted in R.rc (reverse start hints stay unknown).
+// entry.  Matches are also counted in R.hc (reverse start hints stay unknown).
 // The tile's entries are left in LDS (xs) as by dense_flags.
 __device__ uint32_t search_flags(const uint32_t *__restrict__ X, const uint32_t *__restrict__ Y, uint32_t ylo,
                                  uint32_t yhi, uint32_t np, uint32_t B, HubLds &L, uint32_t j0, uint32_t cnt,
@@ -575,11 +621,7 @@ __device__ uint32_t search_flags(const uint32_t *__restrict__ X, const uint32_t 
             const bool hit = i < cnt && p[k] < yhi && Y[p[k]] == x[k];
             L.a.d.flag[i] = hit ? 1 : 0;
             c += hit ? (h + k < 4 ? 0x10001u : 1u) : 0u;  // rows 0..3: the tile's first 256 entries
-            if (R.rseg && hit) {
-                const uint32_t q = p[k] / R.rseg;
-                atomicAdd(&R.rc[q], 1u);
-                if (p[k] - q * R.rseg < R.rseg / 2) atomicAdd(&R.r1[q], 1u);
-            }
+            if (R.half && hit) atomicAdd(&R.hc[p[k] / R.half], 1u);
             if (h + k == 0) first = p[k];
         }
     }
@@ -718,21 +760,30 @@ __device__ __forceinline__ uint64_t wseg_pi(const JobCtx &J, uint64_t wall, uint
 }
 
 // Reverse sketch to collect while merging a cold move at v (a hub) from t.
-__device__ __forceinline__ uint16_t *rev_setup(const Exec &E, const WS &st, uint32_t *rc, uint32_t *rh, uint32_t *r1,
-                                               RevSketch &R)
+__device__ __forceinline__ uint16_t *rev_setup(const Exec &E, const WS &st, uint32_t *hc, uint32_t *rh, RevSketch &R)
 {
-    R.rseg = 0;
+    R.half = 0;
     R.shift = hint_shift(st.vd);
-    R.rc = rc;
+    R.hc = hc;
     R.rh = rh;
-    R.r1 = r1;
     // weighted rows need the weights of N(t), which a merge of N(v) does not read
     if (E.g.wt || st.td < E.g.memo_min || st.td > MEMO_MAX_DEG) return nullptr;
     const uint32_t tsub = (st.td + TX - 1) / TX;
     const uint32_t tG = (tsub + NSUPER - 1) / NSUPER;
-    R.rseg = tG * TX;
+    R.half = tG * (TX / 2);
     R.nsp = memo_segs(st.td);
     return sketch_row(E, st.t, st.td, st.jprev);
+}
+
+// Writes the reverse sketch's row of a vertex of degree td (a wavefront).
+__device__ __forceinline__ void rev_store(const RevSketch &R, uint32_t td, uint16_t *row)
+{
+    const uint32_t l = lane_id();
+    if (!row || l >= (td + 2 * R.half - 1) / (2 * R.half)) return;
+    const uint32_t c1 = R.hc[2 * l], c2 = R.hc[2 * l + 1];
+    __builtin_nontemporal_store((uint16_t)(c1 + c2 + 1), row + l);
+    __builtin_nontemporal_store((uint16_t)R.rh[l], row + R.nsp + l);
+    __builtin_nontemporal_store((uint16_t)(c1 + 1), row + 2 * R.nsp + l);
 }
 
 // Dense inverse CDF of a second-order move over all of N(v): per-segment sums
@@ -788,34 +839,32 @@ __device__ uint32_t hub_dense(const Exec &E, const JobCtx &J, const WS &st, HubL
         }
         warm = ballot(known == 0) == 0;
     }
-    uint64_t S;
+    uint64_t pi = 0;  // per segment (lane): its sum
     if (warm) {
-        uint64_t pi = 0;
         if ((uint32_t)l < nsup) {
             const uint32_t a = l * seglen;
             const uint32_t len = dv - a < seglen ? dv - a : seglen;
             if (W) pi = wseg_pi(J, segw, segcw, pos_t >= a && pos_t - a < len ? wt_t : 0u);
             else pi = seg_pi(J, pos_t, a, len, known - 1);
-            L.b.csum[l] = pi;
         }
-        S = wave_sum(pi);
     } else {
         RevSketch R;
         uint16_t *rrow = nullptr;
-        if (row) rrow = rev_setup(E, st, L.a.d.rc, L.a.d.rh, L.a.d.r1, R);
-        else R.rseg = 0;
-        if (R.rseg) {
-            L.a.d.rc[l] = 0;
+        if (row) rrow = rev_setup(E, st, L.a.d.hc, L.a.d.rh, R);
+        else R.half = 0;
+        if (R.half) {
+            L.a.d.hc[l] = 0;
+            L.a.d.hc[WAVE + l] = 0;
             L.a.d.rh[l] = 0;
-            L.a.d.r1[l] = 0;
+            wave_lds_sync();
         }
         // N(t) much longer than N(v): search N(v)'s entries in it instead of
         // streaming it (reverse start hints then stay unknown)
         const bool srch = (uint64_t)td > (uint64_t)E.search_ratio * dv;
         const uint32_t B = srch ? load_pivots(Y, 0, td, L, NPIV) : 0;
-        uint32_t ypos = !srch && td ? wave_lower_bound(Y, td, X[0]) : 0;
+        uint32_t ypos = uni(!srch && td ? wave_lower_bound(Y, td, X[0]) : 0);
+        R.begin(ypos);
         uint32_t mine = 0;
-        S = 0;
         for (uint32_t sp = 0; sp < nsup; ++sp) {
             uint64_t sum = 0;
             uint32_t csp = 0, c1 = 0;  // members in the segment and in its first half
@@ -833,8 +882,10 @@ __device__ uint32_t hub_dense(const Exec &E, const JobCtx &J, const WS &st, HubL
                     uint32_t lb0;
                     c = search_flags(X, Y, 0, td, NPIV, B, L, j0, cnt, R, lb0);
                     if (sub == sp * G && (uint32_t)l == sp) ystart = lb0;
+                } else if (W) {
+                    c = dense_flags<true>(X, Y, td, L, j0, cnt, ypos, R);
                 } else {
-                    c = dense_flags(X, Y, td, L, j0, cnt, ypos, R);
+                    c = dense_flags<false>(X, Y, td, L, j0, cnt, ypos, R);
                 }
                 const uint32_t ct = c & 0xFFFFu;
                 if (W) {
@@ -852,8 +903,8 @@ __device__ uint32_t hub_dense(const Exec &E, const JobCtx &J, const WS &st, HubL
                 c1 += j0 + cnt <= mid ? ct : (j0 < mid ? c >> 16 : 0u);
                 wave_lds_sync();
             }
-            if (l == 0) L.b.csum[sp] = sum;
             if ((uint32_t)l == sp) {
+                pi = sum;
                 mine = csp;
                 segcnt = csp;
                 halfv = c1 + 1;
@@ -862,7 +913,6 @@ __device__ uint32_t hub_dense(const Exec &E, const JobCtx &J, const WS &st, HubL
                 segw1 = sw1;
                 segcw1 = scw1;
             }
-            S += sum;
         }
         if (row && (uint32_t)l < nsup) {
             __builtin_nontemporal_store((uint16_t)(mine + 1), row + l);
@@ -876,28 +926,26 @@ __device__ uint32_t hub_dense(const Exec &E, const JobCtx &J, const WS &st, HubL
             }
         }
         ycap = ystart;
-        const uint32_t rsup = R.rseg ? (td + R.rseg - 1) / R.rseg : 0;
-        if (rrow && (uint32_t)l < rsup) {
-            __builtin_nontemporal_store((uint16_t)(L.a.d.rc[l] + 1), rrow + l);
-            __builtin_nontemporal_store((uint16_t)L.a.d.rh[l], rrow + R.nsp + l);
-            __builtin_nontemporal_store((uint16_t)(L.a.d.r1[l] + 1), rrow + 2 * R.nsp + l);
-        }
+        R.end();
+        wave_lds_sync();
+        rev_store(R, td, rrow);
     }
     wave_lds_sync();
-    const uint64_t r = hi64(R1, S);
-    uint64_t base;
+    // S, the draw and its segment from one scan (32 bits where the row's sum fits)
+    uint64_t r, base;
     uint32_t spx = nsup - 1;
-    {
-        const uint64_t c = (uint32_t)l < nsup ? L.b.csum[l] : 0;
-        const uint64_t inc = wave_incl_scan(c);
+    if (!W && dv < 1u << 27) {
+        const uint32_t inc = wave_incl_scan32((uint32_t)pi);
+        r = hi64_32((uint32_t)(R1 >> 32), (uint32_t)R1, lane_val(inc, WAVE - 1));
+        const uint64_t m = ballot((uint32_t)l < nsup && inc > (uint32_t)r);
+        if (m) spx = first_lane(m);
+        base = lane_val(inc - (uint32_t)pi, (int)spx);
+    } else {
+        const uint64_t inc = wave_incl_scan(pi);
+        r = hi64(R1, lane_val64(inc, WAVE - 1));
         const uint64_t m = ballot((uint32_t)l < nsup && inc > r);
-        if (m) {
-            const int f = first_lane(m);
-            spx = f;
-            base = lane_val64(inc - c, f);
-        } else {
-            base = lane_val64(inc - c, (int)(nsup - 1));
-        }
+        if (m) spx = first_lane(m);
+        base = lane_val64(inc - pi, (int)spx);
     }
     wave_lds_sync();
     // the matches of segment spx lie in N(t)[ypos, yend): from its start to
@@ -945,7 +993,7 @@ __device__ uint32_t hub_dense(const Exec &E, const JobCtx &J, const WS &st, HubL
     const bool srch = (uint64_t)(yend - ypos) > (uint64_t)E.search_ratio * (xb - xa);
     const uint32_t np = pivots_for(xb - xa);
     const uint32_t B = srch ? load_pivots(Y, ypos, yend, L, np) : 0;
-    const RevSketch none = {};
+    RevSketch none = {};
     for (uint32_t j0 = xa; j0 < xb; j0 += TX) {
         const uint32_t cnt = xb - j0 < (uint32_t)TX ? xb - j0 : (uint32_t)TX;
         uint32_t wrun[XPL];
@@ -954,7 +1002,7 @@ __device__ uint32_t hub_dense(const Exec &E, const JobCtx &J, const WS &st, HubL
             uint32_t lb0;
             search_flags(X, Y, ypos, yend, np, B, L, j0, cnt, none, lb0);
         } else {
-            dense_flags(X, Y, td, L, j0, cnt, ypos, none);
+            dense_flags<true>(X, Y, td, L, j0, cnt, ypos, none);
         }
         const uint32_t j = dense_chunk_locate(wrun, J, pos_t, L, j0, cnt, base, r);
         if (j != SENT) xj = L.a.d.xs[j - j0];  // the chosen neighbour, still in the tile
@@ -1162,9 +1210,8 @@ struct BlkLds {
     uint64_t csum[NSUPER];   // per-segment sums of pi
     uint32_t ystart[NSUPER]; // per-segment start in N(t) (SENT: search)
     uint32_t ycap[NSUPER];   // an index at or above each segment's start
-    uint32_t rc[NSUPER];     // reverse sketch counts
+    uint32_t hc[2 * NSUPER]; // reverse sketch counts per half segment
     uint32_t rh[NSUPER];     // reverse sketch hints
-    uint32_t r1[NSUPER];     // reverse sketch first-half counts
     uint64_t part[HWAVES];   // tile sums of one locate round
     uint32_t q;              // dequeued item
     uint32_t warm;
@@ -1214,22 +1261,23 @@ __device__ __forceinline__ uint32_t block_dense(const Exec &E, const JobCtx &J, 
         }
         B.ystart[l] = ys;
         B.ycap[l] = yc;
-        B.rc[l] = 0;
+        B.hc[l] = 0;
+        B.hc[WAVE + l] = 0;
         B.rh[l] = 0;
-        B.r1[l] = 0;
         if (l == 0) B.warm = warm;
     }
     __syncthreads();
     if (!B.warm) {
         RevSketch R;
         uint16_t *rrow = nullptr;
-        if (row) rrow = rev_setup(E, st, B.rc, B.rh, B.r1, R);
-        else R.rseg = 0;
+        if (row) rrow = rev_setup(E, st, B.hc, B.rh, R);
+        else R.half = 0;
         const uint32_t sp0 = wv * nsup / HWAVES, sp1 = (wv + 1) * nsup / HWAVES;
         const bool srch = (uint64_t)td > (uint64_t)E.search_ratio * dv;
         if (sp0 < sp1) {
             const uint32_t Bp = srch ? load_pivots(Y, 0, td, L, NPIV) : 0;
-            uint32_t ypos = !srch && td ? wave_lower_bound(Y, td, X[sp0 * seglen]) : 0;
+            uint32_t ypos = uni(!srch && td ? wave_lower_bound(Y, td, X[sp0 * seglen]) : 0);
+            R.begin(ypos);
             for (uint32_t sp = sp0; sp < sp1; ++sp) {
                 uint64_t sum = 0;
                 uint32_t csp = 0;
@@ -1244,7 +1292,8 @@ __device__ __forceinline__ uint32_t block_dense(const Exec &E, const JobCtx &J, 
                         c = search_flags(X, Y, 0, td, NPIV, Bp, L, j0, cnt, R, lb0) & 0xFFFFu;
                         if (sub == sp * G) ys = lb0;
                     } else {
-                        c = dense_flags(X, Y, td, L, j0, cnt, ypos, R) & 0xFFFFu;
+                        c = (W ? dense_flags<true>(X, Y, td, L, j0, cnt, ypos, R)
+                               : dense_flags<false>(X, Y, td, L, j0, cnt, ypos, R)) & 0xFFFFu;
                     }
                     sum += W ? dense_chunk_sum(W, J, pos_t, L, j0, cnt) : seg_pi(J, pos_t, j0, cnt, c);
                     csp += c;
@@ -1260,14 +1309,10 @@ __device__ __forceinline__ uint32_t block_dense(const Exec &E, const JobCtx &J, 
                     }
                 }
             }
+            R.end();
         }
         __syncthreads();
-        const uint32_t rsup = R.rseg ? (td + R.rseg - 1) / R.rseg : 0;
-        if (wv == 0 && rrow && (uint32_t)l < rsup) {
-            __builtin_nontemporal_store((uint16_t)(B.rc[l] + 1), rrow + l);
-            __builtin_nontemporal_store((uint16_t)B.rh[l], rrow + R.nsp + l);
-            __builtin_nontemporal_store((uint16_t)(B.r1[l] + 1), rrow + 2 * R.nsp + l);
-        }
+        if (wv == 0) rev_store(R, td, rrow);
     }
     // every wavefront finds the same segment from the shared sums
     const uint64_t c = (uint32_t)l < nsup ? B.csum[l] : 0;
@@ -1285,7 +1330,7 @@ __device__ __forceinline__ uint32_t block_dense(const Exec &E, const JobCtx &J, 
     if (yhi < ylo) yhi = ylo;
     const uint32_t xlen = dv - spx * seglen < seglen ? dv - spx * seglen : seglen;
     const bool lsrch = (uint64_t)(yhi - ylo) > (uint64_t)E.search_ratio * xlen;
-    const RevSketch none = {};
+    RevSketch none = {};
     const uint32_t sub_end = nsub < (spx + 1) * G ? nsub : (spx + 1) * G;
     const uint32_t Bl = lsrch && spx * G + wv < sub_end ? load_pivots(Y, ylo, yhi, L, NPIV) : 0;
     for (uint32_t b = spx * G; b < sub_end; b += HWAVES) {
@@ -1302,7 +1347,7 @@ __device__ __forceinline__ uint32_t block_dense(const Exec &E, const JobCtx &J, 
             } else {
                 uint32_t ypos = ylo;
                 if (sub != spx * G) ypos = ylo + wave_lower_bound(Y + ylo, yhi - ylo, X[j0]);
-                cc = dense_flags(X, Y, td, L, j0, cnt, ypos, none) & 0xFFFFu;
+                cc = dense_flags<true>(X, Y, td, L, j0, cnt, ypos, none) & 0xFFFFu;
             }
             tsum = W ? dense_chunk_sum(W, J, pos_t, L, j0, cnt) : seg_pi(J, pos_t, j0, cnt, cc);
         }
