@@ -1576,6 +1576,29 @@ __device__ __forceinline__ Exec exec_for(const Exec &E)
     return e;
 }
 
+// Lanes of a wavefront that take walks.  Where hub moves are common a
+// wavefront makes them one after the other: the walks that share it wait for
+// each other, and a wavefront that meets many holds up the launch's end.  So
+// the more of the entries lie in hub rows (lane_div), the smaller a part of
+// its walks a wavefront starts at once (eight where it has eight); the rest go
+// to whoever is free.  Measured with all walks started by index / half / a
+// quarter / an eighth of them: 48 walks per wavefront at scale 18 without
+// sketches 34.8 / 34.2 / 29.2 / 28.6 ms, 8 per wavefront at scale 16 1.41 /
+// 1.38 / 1.43 / 1.61 ms.
+__device__ __forceinline__ uint32_t walk_lanes(const Exec &E, uint32_t q)
+{
+    const uint32_t part = (q + E.lane_div - 1) / E.lane_div;
+    return q < 8u || part > (uint32_t)WAVE ? (uint32_t)WAVE : (part < 8u ? 8u : part);
+}
+
+// Walks each wavefront of a launch takes by its own index, of q for each; 0:
+// all of them are given out so, evenly.
+__device__ __forceinline__ uint32_t first_share(const Exec &E, uint32_t q, uint32_t lanes)
+{
+    if (lanes >= q) return 0;
+    return E.lane_div > 1 ? lanes : (q < (uint32_t)POOL ? q : (uint32_t)POOL);
+}
+
 template <class Src, bool WALKS, bool COUNTS, Kind K>
 __global__ __launch_bounds__(PBLOCK, 5) void k_persistent(Exec E_arg, Src S)
 {
@@ -1587,15 +1610,22 @@ __global__ __launch_bounds__(PBLOCK, 5) void k_persistent(Exec E_arg, Src S)
     const int l = lane_id();
     const uint32_t total = S.total();
     const uint32_t tw = E.t_wave < E.g.d_rule ? E.t_wave : E.g.d_rule;
-    uint32_t pool_next = 0, pool_end = 0;  // walks this wavefront has claimed but not started
-    // claims of up to POOL walks, but small enough that every wavefront of the
-    // grid gets some (wave-class moves of a wavefront's walks run one by one);
-    // later claims shrink with what is left (guided self-scheduling, down to
-    // one walk), so that no wavefront holds unstarted walks while others have
-    // run dry
+    // Walks this wavefront has claimed but not started.  The first claim is its
+    // share by its own index, at most POOL walks, and costs nothing: where
+    // every wavefront took even its first walk from the counter, 10,000 walks
+    // spent 0.2 ms on its atomics.  Later claims come from the counter and
+    // shrink with what is left (guided self-scheduling, down to one walk), so
+    // that no wavefront holds unstarted walks while others have run dry.
     const uint32_t nwaves = gridDim.x * (PBLOCK / WAVE);
-    uint32_t pool = total / nwaves < 1u ? 1u : (total / nwaves < (uint32_t)POOL ? total / nwaves : (uint32_t)POOL);
-    bool exhausted = false;
+    const uint32_t wid = blockIdx.x * (PBLOCK / WAVE) + threadIdx.x / WAVE;
+    const uint32_t lanes = walk_lanes(E, total / nwaves);
+    const uint32_t share0 = first_share(E, total / nwaves, lanes);
+    const uint32_t given = share0 ? nwaves * share0 : total;  // walks given out by index
+    uint32_t pool_next = share0 ? wid * share0 : (uint32_t)((uint64_t)total * wid / nwaves);
+    uint32_t pool_end = share0 ? pool_next + share0 : (uint32_t)((uint64_t)total * (wid + 1) / nwaves);
+    const uint32_t left = given < total ? (total - given) / (2 * nwaves) : 0u;
+    uint32_t pool = left < 1u ? 1u : (left < share0 ? left : share0);
+    bool exhausted = given >= total;
     uint64_t csum = 0;
     sl[l].flags = 0;
     for (;;) {
@@ -1609,14 +1639,14 @@ __global__ __launch_bounds__(PBLOCK, 5) void k_persistent(Exec E_arg, Src S)
             if (live) slot_to_ws(E, q, st);
             // idle lanes start walks claimed from the global counter, pool at a time
             for (;;) {
-                const uint64_t m = ballot(!live);
+                const uint64_t m = ballot(!live && (uint32_t)l < lanes);
                 if (m == 0) break;
                 if (pool_next >= pool_end) {
                     if (exhausted) break;
                     const uint32_t claim = pool;
                     uint32_t b = 0;
                     if (l == 0) b = atomicAdd(S.cursor(), claim);
-                    b = uni(b);
+                    b = given + uni(b);
                     if (b >= total) {
                         exhausted = true;
                         break;
@@ -1628,7 +1658,7 @@ __global__ __launch_bounds__(PBLOCK, 5) void k_persistent(Exec E_arg, Src S)
                 }
                 const uint32_t avail = pool_end - pool_next;
                 const uint32_t r = __popcll(m & lanemask_lt());
-                if (!live && r < avail) {
+                if (!live && (uint32_t)l < lanes && r < avail) {
                     uint32_t job, i;
                     S.locate(pool_next + r, job, i);
                     const JobCtx J = S.ctx(job);
@@ -1661,7 +1691,7 @@ __global__ __launch_bounds__(PBLOCK, 5) void k_persistent(Exec E_arg, Src S)
                 if (act == 0) break;
                 // past the budget, back to the wave phase and to claiming as
                 // soon as some lane waits for either
-                if (it >= E.thread_iters && act != ~0ull && (!exhausted || ballot(pend))) break;
+                if (it >= E.thread_iters && ((!exhausted && (uint32_t)__popcll(act) < lanes) || ballot(pend))) break;
                 if (!can) continue;
                 uint32_t j;
                 Nb b;
@@ -2005,28 +2035,42 @@ size_t plain_ws(uint32_t n_starts, uint32_t L)
     return c.total();
 }
 
-uint32_t persistent_blocks(const n2v_exec_opts &o, int dev, uint64_t walks)
+uint32_t persistent_blocks(const n2v_exec_opts &o, int dev, uint64_t walks, bool few_hubs)
 {
     DevInfo &d = dev_info(dev);
     uint32_t per_cu = o.waves_per_cu ? (o.waves_per_cu + (PBLOCK / WAVE) - 1) / (PBLOCK / WAVE) : (uint32_t)d.occ;
     if (per_cu > (uint32_t)d.occ) per_cu = d.occ;
     if (per_cu < 1) per_cu = 1;
     uint64_t blocks = (uint64_t)d.cus * per_cu;
-    const uint64_t need = (walks + WAVE - 1) / WAVE;  // small jobs: spread walks thin over more wavefronts
+    // Small jobs: down to a wavefront per walk.  Past a walk per wavefront, a
+    // job with hardly any hub moves fills its lanes first (but for two wavefronts per
+    // SIMD, which hide each other's latency): rounds with part of the lanes
+    // cost as many instructions (112,086 walks, weighted, degree 100: 0.90
+    // against 1.00 ms).
+    uint64_t waves = walks;
+    if (few_hubs && walks > blocks * (PBLOCK / WAVE)) waves = std::max<uint64_t>(walks / WAVE, 8ull * d.cus);
+    const uint64_t need = (waves + PBLOCK / WAVE - 1) / (PBLOCK / WAVE);
     if (blocks > need) blocks = need;
     if (blocks < 1) blocks = 1;
     return (uint32_t)blocks;
 }
 
 template <bool W, bool C>
-int launch_persistent(const Exec &E, const OneJob &S, const n2v_exec_opts &o, int dev, hipStream_t st)
+int launch_persistent(const Exec &E_opts, const OneJob &S, const n2v_exec_opts &o, int dev, hipStream_t st)
 {
+    Exec E = E_opts;
+    const uint32_t blocks = persistent_blocks(o, dev, S.n, E.thread_iters > 4);
+    // A walk alone on its wavefront lasts as long as its chain of attempts:
+    // the wavefront makes 64 of a move at once (1000 walks of 40 moves on
+    // ER-20: 139 -> 75 us).  Not where hubs are common, whose lines the other
+    // 60 attempts' reads push out (100 walks at scale 16: 165 against 194 us).
+    if (E.lane_div == 1 && S.n <= blocks * (PBLOCK / WAVE)) E.t_wave = 0;
     hipLaunchKernelGGL(k_zero, dim3(1), dim3(64), 0, st, S.cur, 1u);
     const Kind K = kind_of(E);
     auto kernel = K == WEIGHTED       ? k_persistent<OneJob, W, C, WEIGHTED>
                   : K == WIDE_ENTRIES ? k_persistent<OneJob, W, C, WIDE_ENTRIES>
                                       : k_persistent<OneJob, W, C, PLAIN_ENTRIES>;
-    hipLaunchKernelGGL(kernel, dim3(persistent_blocks(o, dev, S.n)), dim3(PBLOCK), 0, st, E, S);
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(PBLOCK), 0, st, E, S);
     N2V_HIP(hipGetLastError());
     return N2V_OK;
 }
@@ -2201,13 +2245,16 @@ void make_exec(const n2v_graph *g, const n2v_exec_opts &o, Exec *E)
     // 15.5 ms, WeC-22 28.6 / 27.9 / 27.5 ms.
     const uint64_t he = g->hub_entries, m = g->dg.m;
     E->thread_iters = he && he * 20 >= m * 7 ? 2u : (he && he * 50 >= m ? 4u : 64u);
+    // 1 up to 10% of the entries in hub rows, 8 from 40% (see walk_lanes)
+    const uint64_t twentieths = m ? he * 20 / m : 0;
+    E->lane_div = twentieths < 1 ? 1u : (twentieths > 8 ? 8u : (uint32_t)twentieths);
 }
 
 PlainKey plain_key(const Exec &E, const OneJob &S, const void *ws, uint32_t hub_blocks, bool W, bool C)
 {
     // every field the launches read from the host: a new field of Exec,
     // DevGraph, JobCtx or OneJob must be added here
-    static_assert(sizeof(DevGraph) == 128 && sizeof(Exec) == 160 && sizeof(JobCtx) == 56 && sizeof(OneJob) == 80,
+    static_assert(sizeof(DevGraph) == 128 && sizeof(Exec) == 168 && sizeof(JobCtx) == 56 && sizeof(OneJob) == 80,
                   "plain_key covers every launch argument");
     PlainKey k;
     const DevGraph &d = E.g;
@@ -2229,7 +2276,7 @@ PlainKey plain_key(const Exec &E, const OneJob &S, const void *ws, uint32_t hub_
     k.put2(E.t_wave, E.t_sparse);
     k.put2(E.sparse_ratio, E.t_wg);
     k.put2(E.search_ratio, hub_blocks);
-    k.put2(E.thread_iters, 0u);
+    k.put2(E.thread_iters, E.lane_div);
     k.put(E.cursor);
     k.put(S.c.out);
     k.put(S.c.cnt);
