@@ -154,7 +154,7 @@ typedef struct {
     int mode;            /* N2V_MODE_*; AUTO = PERSISTENT */
     uint32_t t_wave;     /* persistent: rejection moves at degree > t_wave run wave-cooperatively */
     uint32_t t_sparse;   /* hub moves use the sparse intersection when deg(t) <= t_sparse (default
-                            1023, the most the sparse path holds) ... */
+                            1023; the sparse path holds 895) ... */
     uint32_t sparse_ratio; /* ... and deg(t) * sparse_ratio * log2(deg v) < deg(v) + deg(t) */
     uint32_t waves_per_cu; /* persistent grid size (0: occupancy-derived) */
     uint32_t block;      /* workgroup size (256) */

@@ -247,10 +247,16 @@ __device__ __forceinline__ uint64_t lower_bound_g(const uint32_t *__restrict__ a
     return lo;
 }
 
-__device__ __forceinline__ bool contains_g(const uint32_t *__restrict__ a, uint64_t lo, uint64_t hi, uint32_t x)
+// Whether the sorted row[0, n) holds x.
+__device__ __forceinline__ bool row_contains(const uint32_t *__restrict__ row, uint32_t n, uint32_t x)
 {
-    const uint64_t p = lower_bound_g(a, lo, hi, x);
-    return p < hi && a[p] == x;
+    uint32_t lo = 0, hi = n;
+    while (lo < hi) {
+        const uint32_t mid = lo + ((hi - lo) >> 1);
+        if (row[mid] < x) lo = mid + 1;
+        else hi = mid;
+    }
+    return lo < n && row[lo] == x;
 }
 
 // ------------------------------------------------- membership filter

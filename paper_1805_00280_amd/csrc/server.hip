@@ -177,7 +177,7 @@ struct n2v_server {
     {
         N2V_HIP(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
         hipError_t e1 = hipMemcpyAsync(t.dev, t.host, sizeof(TableHdr), hipMemcpyHostToDevice, st);
-        int rc = launch_job_table(E, t.dev, full_grid_blocks(g->device), st);
+        int rc = launch_job_table(E, t.dev, full_grid_blocks(E, g->device), st);
         hipGraph_t graph = nullptr;
         hipError_t e2 = hipStreamEndCapture(st, &graph);
         if (e1 != hipSuccess) return hip_fail(e1, "hipMemcpyAsync (capture)");

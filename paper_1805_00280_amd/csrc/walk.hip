@@ -61,10 +61,15 @@ static_assert(XPL == 8, "a lane's run of tile flags is read as one u64");
 constexpr int YPL = 8;              // dense merge: later N(t) blocks of 8 x 64 entries
 constexpr int YFIRST = 4;           // entries per lane of the first N(t) block of a tile
 constexpr int NSUPER = MEMO_SEGS;   // segments (sums) per hub row
-constexpr int SPCAP = 1024;         // specials (positions) held by the sparse path
+// Specials (positions) held by the sparse path, so one more than the largest
+// N(t) it takes.  Holding 1024 with half the pivots instead measured scale 22
+// skewed 413 against 353 ms (those rows' members are many; the dense path
+// merges them faster), scale 18 without sketches and Skew-5 level.
+constexpr int SPCAP = 896;
 constexpr int NPIV = 256;           // pivots of an N(t) range that N(v) entries are searched in
 
-// LDS of one wavefront for hub moves (5 KiB).
+// LDS of one wavefront for hub moves (4.5 KiB: with the lanes' slots, six
+// workgroups of four wavefronts fit a CU).
 struct HubLds {
     union {
         struct {
@@ -154,6 +159,7 @@ struct Cols {
 };
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint16_t u16x8 __attribute__((ext_vector_type(8), aligned(2)));
 
 // Stores the entries of columns (col - n, col] of walk i.
 template <bool WALKS>
@@ -305,7 +311,7 @@ __device__ __forceinline__ bool maybe_member(const Exec &E, const WS &st, uint32
 // Whether x is a neighbour of t.
 __device__ __forceinline__ bool is_member(const Exec &E, const WS &st, uint32_t x)
 {
-    return maybe_member(E, st, x) && contains_g(E.g.adj, st.to, st.to + st.td, x);
+    return maybe_member(E, st, x) && row_contains(E.g.adj + st.to, st.td, x);
 }
 
 // One rejection attempt k; returns whether it accepts, its neighbour index,
@@ -409,41 +415,74 @@ struct RevSketch {
         acc = 0;
     }
 
-    // Lanes 0 .. nin-1 hold indices y0 + lane of N(t), M the hits among them,
-    // p the lane's lower bound in N(v).
-    __device__ __forceinline__ void count(uint32_t y0, uint32_t nin, uint64_t M, uint32_t p)
+    // Lane l holds indices y0 + 4 l + k of N(t), the first nin of them in the
+    // stream; M[k] the hits, p[k] the lane's lower bounds in N(v).
+    __device__ __forceinline__ void count(uint32_t y0, uint32_t nin, const uint64_t (&M)[4], const uint32_t (&p)[4])
     {
         if (!half) return;
+        const uint32_t all = (uint32_t)(__popcll(M[0]) + __popcll(M[1]) + __popcll(M[2]) + __popcll(M[3]));
         const uint32_t nb = next - y0;
-        if (nb < nin) {
-            const uint64_t before = M & ((1ull << nb) - 1ull);
-            acc += (uint32_t)__popcll(before);
-            if (acc && lane_id() == 0) atomicAdd(&hc[at], acc);
-            at += 1;
-            next += half;
-            acc = (uint32_t)__popcll(M ^ before);
-            if (!(at & 1u) && lane_id() == (int)nb) rh[at >> 1] = (p >> shift) + 1;
-        } else {
-            acc += (uint32_t)__popcll(M);
+        if (nb >= nin) {
+            acc += all;
+            return;
+        }
+        uint32_t before = 0;
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k) {
+            const uint32_t lanes = (nb + 3 - k) >> 2;  // those with 4 l + k < nb
+            before += (uint32_t)__popcll(lanes < (uint32_t)WAVE ? M[k] & ((1ull << lanes) - 1ull) : M[k]);
+        }
+        acc += before;
+        if (acc && lane_id() == 0) atomicAdd(&hc[at], acc);
+        at += 1;
+        next += half;
+        acc = all - before;
+        if (!(at & 1u) && lane_id() == (int)(nb >> 2)) {
+            const uint32_t k = nb & 3u;
+            const uint32_t q = k == 0 ? p[0] : (k == 1 ? p[1] : (k == 2 ? p[2] : p[3]));
+            rh[at >> 1] = (q >> shift) + 1;
         }
     }
 };
 
-// Looks a block of NB x 64 entries of N(t), loaded from ypos (0xFFFFFFFF past
-// the end), up in the staged tile; returns how many lie in the tile's value
-// range (they form a prefix of the block, N(t) being sorted).  The lower
-// bounds in the tile are found by branchless searches that advance SEARCH_ILP
-// entries per lane in lockstep, so their LDS reads overlap instead of each
-// probe waiting for the previous one.  FLAGS marks the hits' tile entries;
-// without, c counts them, those among the tile's first 256 entries also in
-// its upper half.
+// Lane l's run of entries 4 l .. 4 l + 3 of each 256-entry group of p[0, n)
+// (0xFFFFFFFF past n): one 16-byte read per group where the group is whole.
+template <int NB>
+__device__ __forceinline__ void load_runs(const uint32_t *__restrict__ p, uint32_t n, uint32_t (&y)[NB])
+{
+    static_assert(NB % 4 == 0, "groups of 4 entries per lane");
+    const uint32_t i = 4u * (uint32_t)lane_id();
+    if (n >= (uint32_t)(NB * WAVE)) {
+#pragma unroll
+        for (int g = 0; g < NB; g += 4) {
+            const u32x4 v = *(const u32x4 *)(p + g * WAVE + i);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) y[g + k] = v[k];
+        }
+    } else {
+#pragma unroll
+        for (int g = 0; g < NB; ++g) {
+            const uint32_t e = (g & ~3) * WAVE + i + (g & 3);
+            y[g] = e < n ? p[e] : 0xFFFFFFFFu;
+        }
+    }
+}
+
+// Looks a block of NB x 64 entries of N(t), loaded from ypos by load_runs, up
+// in the staged tile; returns how many lie in the tile's value range (they
+// form a prefix of the block, N(t) being sorted).  The lower bounds in the
+// tile are found by branchless searches that advance SEARCH_ILP entries per
+// lane in lockstep, so their LDS reads overlap instead of each probe waiting
+// for the previous one.  FLAGS marks the hits' tile entries; without, c
+// counts them, those among the tile's first 256 entries also in its upper
+// half.
 constexpr int SEARCH_ILP = 4;
 
 template <int NB, bool FLAGS>
 __device__ __forceinline__ uint32_t flag_block(HubLds &L, const uint32_t (&y)[NB], uint32_t ypos, uint32_t j0,
                                                uint32_t xlast, RevSketch &R, uint32_t &c)
 {
-    static_assert(NB % SEARCH_ILP == 0, "blocks are searched SEARCH_ILP entries per lane at a time");
+    static_assert(NB % SEARCH_ILP == 0 && SEARCH_ILP == 4, "one group of load_runs is searched at a time");
     uint32_t nin = 0;
 #pragma unroll
     for (int g = 0; g < NB; g += SEARCH_ILP) {
@@ -460,26 +499,33 @@ __device__ __forceinline__ uint32_t flag_block(HubLds &L, const uint32_t (&y)[NB
         uint32_t xq[SEARCH_ILP];
 #pragma unroll
         for (int k = 0; k < SEARCH_ILP; ++k) xq[k] = q[k][0];
+        uint64_t M[SEARCH_ILP];
+        uint32_t at[SEARCH_ILP], in = 0;
 #pragma unroll
         for (int k = 0; k < SEARCH_ILP; ++k) {
             // entries past the tile's range, the padding among them, are out
-            const uint64_t in = ballot(y[g + k] <= xlast);
             const bool hit = xq[k] == y[g + k] && y[g + k] <= xlast;
             const uint32_t pos = (uint32_t)(q[k] - L.a.d.xs);
-            const uint64_t M = ballot(hit);
+            in += (uint32_t)__popcll(ballot(y[g + k] <= xlast));
+            M[k] = ballot(hit);
+            at[k] = j0 + pos;
             if (FLAGS) {
                 if (hit) L.a.d.flag[pos] = 1;
             } else {
-                c += (uint32_t)__popcll(M) + ((uint32_t)__popcll(M & ballot(pos < (uint32_t)TX / 2)) << 16);
+                c += (uint32_t)__popcll(M[k]) + ((uint32_t)__popcll(M[k] & ballot(pos < (uint32_t)TX / 2)) << 16);
             }
-            R.count(ypos + (g + k) * WAVE, (uint32_t)__popcll(in), M, j0 + pos);
-            nin += (uint32_t)__popcll(in);
         }
-        if (nin < (uint32_t)((g + SEARCH_ILP) * WAVE)) break;  // the rest of the block lies beyond the tile
+        R.count(ypos + g * WAVE, in, M, at);
+        nin += in;
+        if (in < (uint32_t)(SEARCH_ILP * WAVE)) break;  // the rest of the block lies beyond the tile
     }
     return nin;
 }
 
+// Tiles and blocks are read 16 bytes per lane and written to LDS likewise (a
+// word per lane and read took 16 reads, each with its bounds check: scale 22
+// skewed 393 -> 373 ms, scale 18 without sketches 28.8 -> 27.3 ms, visit counts
+// at scale 21 137 -> 134 ms).
 // Stages N(v)[j0, j0+cnt) (cnt <= TX) in LDS and finds the members of N(t),
 // streaming N(t) from ypos (advanced past every value <= the tile's last
 // entry).  The tile and a first, small block of N(t) are loaded together
@@ -495,18 +541,11 @@ __device__ __forceinline__ uint32_t dense_flags(const uint32_t *__restrict__ X, 
 {
     const int l = lane_id();
     uint32_t xv[XPL], y0[YFIRST];
+    load_runs<XPL>(X + j0, cnt, xv);
+    load_runs<YFIRST>(Y + ypos, ypos < td ? td - ypos : 0u, y0);
 #pragma unroll
-    for (int e = 0; e < XPL; ++e) {
-        const uint32_t i = e * WAVE + l;
-        xv[e] = i < cnt ? X[j0 + i] : 0xFFFFFFFFu;
-    }
-#pragma unroll
-    for (int b = 0; b < YFIRST; ++b) {
-        const uint32_t idx = ypos + b * WAVE + l;
-        y0[b] = idx < td ? Y[idx] : 0xFFFFFFFFu;
-    }
-#pragma unroll
-    for (int e = 0; e < XPL; ++e) L.a.d.xs[e * WAVE + l] = xv[e];
+    for (int e = 0; e < XPL; e += 4)
+        *(uint4 *)&L.a.d.xs[e * WAVE + 4 * l] = make_uint4(xv[e], xv[e + 1], xv[e + 2], xv[e + 3]);
     if (FLAGS) *(uint64_t *)&L.a.d.flag[l * XPL] = 0;
     wave_lds_sync();
     const uint32_t xlast = uni(L.a.d.xs[cnt - 1]);
@@ -516,11 +555,7 @@ __device__ __forceinline__ uint32_t dense_flags(const uint32_t *__restrict__ X, 
     if (nin == YFIRST * WAVE) {
         while (ypos < td) {
             uint32_t y[YPL];
-#pragma unroll
-            for (int b = 0; b < YPL; ++b) {
-                const uint32_t idx = ypos + b * WAVE + l;
-                y[b] = idx < td ? Y[idx] : 0xFFFFFFFFu;
-            }
+            load_runs<YPL>(Y + ypos, td - ypos, y);
             nin = flag_block<YPL, FLAGS>(L, y, ypos, j0, xlast, R, c);
             ypos += nin;
             if (nin < YPL * WAVE) break;
@@ -658,49 +693,60 @@ __device__ uint64_t dense_chunk_sum(const uint16_t *__restrict__ W, const JobCtx
 __device__ __forceinline__ void tile_run_weights(const uint16_t *__restrict__ W, uint32_t j0, uint32_t cnt,
                                                  uint32_t (&w)[XPL])
 {
+    if (!W) return;
     const uint32_t i0 = (uint32_t)lane_id() * XPL;
+    if (i0 + XPL <= cnt) {
+        const u16x8 v = *(const u16x8 *)(W + j0 + i0);
 #pragma unroll
-    for (int e = 0; e < XPL; ++e) w[e] = W && i0 + e < cnt ? W[j0 + i0 + e] : (W ? 0u : 1u);
+        for (int e = 0; e < XPL; ++e) w[e] = v[e];
+    } else {
+#pragma unroll
+        for (int e = 0; e < XPL; ++e) w[e] = i0 + e < cnt ? W[j0 + i0 + e] : 0u;
+    }
 }
 
 // First index of the tile whose running prefix (base + partial) exceeds r,
 // or SENT (base then holds the prefix after the tile).  Lane l takes the run
 // of entries [XPL*l, XPL*l + XPL): one 32-bit wave scan of the run sums (a
 // tile sums to at most 512 * 65535 * 16 < 2^32) finds the lane whose run
-// crosses r, and that lane walks its run.
-__device__ uint32_t dense_chunk_locate(const uint32_t (&wrun)[XPL], const JobCtx &J, uint32_t pos_t,
-                                       const HubLds &L, uint32_t j0, uint32_t cnt, uint64_t &base, uint64_t r)
+// crosses r, and that lane counts the entries whose prefix does not.
+template <bool WEIGHTS>
+__device__ __forceinline__ uint32_t dense_chunk_locate(const uint32_t (&wrun)[XPL], const JobCtx &J, uint32_t pos_t,
+                                                       const HubLds &L, uint32_t j0, uint32_t cnt, uint64_t &base,
+                                                       uint64_t r)
 {
     const int l = lane_id();
     const uint32_t i0 = (uint32_t)l * XPL;
-    const uint64_t f8 = *(const uint64_t *)&L.a.d.flag[i0];
+    const uint2 f = *(const uint2 *)&L.a.d.flag[i0];
+    const uint32_t live = cnt > i0 ? cnt - i0 : 0u;  // entries of the run
+    const uint32_t rel = pos_t - (j0 + i0);          // t's place in the run, if below XPL
     uint32_t pi[XPL];
     uint32_t run = 0;
 #pragma unroll
-    for (int e = 0; e < XPL; ++e) {
-        const uint32_t i = i0 + e;
-        const uint32_t w = i < cnt ? wrun[e] : 0u;
-        const uint32_t m = (j0 + i == pos_t) ? J.A_ret : (((f8 >> (8 * e)) & 0xFF) ? A_COM : J.A_out);
-        pi[e] = w * m;
-        run += pi[e];
+    for (uint32_t e = 0; e < (uint32_t)XPL; ++e) {
+        const uint32_t fl = ((e < 4 ? f.x : f.y) >> (8 * (e & 3))) & 1u;
+        uint32_t m = fl ? A_COM : J.A_out;
+        if (e == rel) m = J.A_ret;
+        if (WEIGHTS) m *= wrun[e];  // 0 past the tile
+        else if (e >= live) m = 0;
+        run += m;
+        pi[e] = run;
     }
     const uint32_t inc = wave_incl_scan32(run);
-    const uint64_t m = ballot(base + inc > r);
+    // what is left of r fits 32 bits, or no prefix of the tile exceeds it
+    const uint64_t d = r - base;
+    const uint32_t left = d >> 32 ? 0xFFFFFFFFu : (uint32_t)d;
+    const uint64_t m = ballot(inc > left);
     if (m == 0) {
         base += lane_val(inc, WAVE - 1);
         return SENT;
     }
-    const int f = first_lane(m);
-    uint32_t j = SENT;
-    if (l == f) {
-        uint64_t acc = base + (inc - run);
+    const uint32_t mine = left - (inc - run);  // of the crossing lane: below its run's sum
+    uint32_t k = 0;
 #pragma unroll
-        for (int e = 0; e < XPL; ++e) {
-            acc += pi[e];
-            if (j == SENT && acc > r) j = j0 + i0 + e;
-        }
-    }
-    return lane_val(j, f);
+    for (int e = 0; e < XPL - 1; ++e) k += pi[e] <= mine ? 1u : 0u;
+    const int c = first_lane(m);
+    return j0 + (uint32_t)c * XPL + lane_val(k, c);
 }
 
 // Sum of pi over N(v)[j0, j0+len) of an unweighted row with c members of N(t).
@@ -739,7 +785,7 @@ __device__ __forceinline__ TileW tile_weights(const uint32_t (&wrun)[XPL], const
     uint32_t a = 0, c = 0;
 #pragma unroll
     for (int e = 0; e < XPL; ++e) {
-        const uint32_t w = i0 + e < cnt ? wrun[e] : 0u;
+        const uint32_t w = wrun[e];  // 0 past the tile
         a += w;
         c += ((f8 >> (8 * e)) & 0xFF) ? w : 0u;
     }
@@ -754,7 +800,7 @@ __device__ __forceinline__ TileW tile_weights(const uint32_t (&wrun)[XPL], const
 // pi summed over entries of a weighted row whose weights sum to wall, of which
 // members of N(t) sum to wcom, and t's own weight wt_t when t is among them
 // (A_ret for t, A_com for members, A_out for the rest).
-__device__ __forceinline__ uint64_t wseg_pi(const JobCtx &J, uint64_t wall, uint64_t wcom, uint64_t wt_t)
+__device__ __forceinline__ uint64_t wseg_pi(const JobCtx &J, uint32_t wall, uint32_t wcom, uint32_t wt_t)
 {
     return (uint64_t)J.A_out * (wall - wcom - wt_t) + (uint64_t)A_COM * wcom + (uint64_t)J.A_ret * wt_t;
 }
@@ -808,7 +854,7 @@ __device__ uint32_t hub_dense(const Exec &E, const JobCtx &J, const WS &st, HubL
     // N(t) + 1, the same over the first half + 1, all entries, first half)
     const uint32_t nsp = memo_segs(dv);  // entries per array of the row
     uint32_t *row32 = row && W ? (uint32_t *)(row + 3 * nsp) : nullptr;
-    const uint64_t wt_t = W && pos_t != SENT ? W[pos_t] : 0u;
+    const uint32_t wt_t = W && pos_t != SENT ? W[pos_t] : 0u;
     bool warm = false;
     // per segment (lane): count + 1; where its stream of N(t) may start (SENT:
     // unknown), and an index at or above that start; first-half count + 1 (0:
@@ -1004,7 +1050,8 @@ __device__ uint32_t hub_dense(const Exec &E, const JobCtx &J, const WS &st, HubL
         } else {
             dense_flags<true>(X, Y, td, L, j0, cnt, ypos, none);
         }
-        const uint32_t j = dense_chunk_locate(wrun, J, pos_t, L, j0, cnt, base, r);
+        const uint32_t j = W ? dense_chunk_locate<true>(wrun, J, pos_t, L, j0, cnt, base, r)
+                             : dense_chunk_locate<false>(wrun, J, pos_t, L, j0, cnt, base, r);
         if (j != SENT) xj = L.a.d.xs[j - j0];  // the chosen neighbour, still in the tile
         wave_lds_sync();
         if (j != SENT) return j;
@@ -1361,7 +1408,8 @@ __device__ __forceinline__ uint32_t block_dense(const Exec &E, const JobCtx &J, 
         if (has && before <= r && before + tsum > r) {
             uint32_t wrun[XPL];
             tile_run_weights(W, j0, cnt, wrun);
-            const uint32_t j = dense_chunk_locate(wrun, J, pos_t, L, j0, cnt, before, r);
+            const uint32_t j = W ? dense_chunk_locate<true>(wrun, J, pos_t, L, j0, cnt, before, r)
+                                 : dense_chunk_locate<false>(wrun, J, pos_t, L, j0, cnt, before, r);
             if (l == 0) B.ans = j;
         }
         wave_lds_sync();
@@ -1599,14 +1647,25 @@ __device__ __forceinline__ uint32_t first_share(const Exec &E, uint32_t q, uint3
     return E.lane_div > 1 ? lanes : (q < (uint32_t)POOL ? q : (uint32_t)POOL);
 }
 
+// Six wavefronts per SIMD (80 registers) hide more of the hub moves' latency
+// than five: scale 22 skewed 370 -> 353 ms, FN-Approx on Skew-5 97.6 -> 88.5
+// ms, visit counts at scale 21 132 -> 119 ms, scale 18 without sketches 26.7 ->
+// 24.6 ms.  The weighted moves need 96 registers (four wavefronts with 128:
+// 263 against 215 ms at scale 20); graphs with wide entries, which have hardly
+// any hub moves, spill at 80 (ER-22 11.2 -> 12.1 ms).
 template <class Src, bool WALKS, bool COUNTS, Kind K>
-__global__ __launch_bounds__(PBLOCK, 5) void k_persistent(Exec E_arg, Src S)
+__global__ __launch_bounds__(PBLOCK, K == PLAIN_ENTRIES ? 6 : 5) void k_persistent(Exec E_arg, Src S)
 {
     const Exec E = exec_for<K>(E_arg);
     __shared__ HubLds lds[PBLOCK / WAVE];
     __shared__ Slot slots[PBLOCK / WAVE][WAVE];
-    HubLds &L = lds[threadIdx.x / WAVE];
-    Slot *sl = slots[threadIdx.x / WAVE];
+    // the wavefront's number in a scalar: its LDS addresses stay out of the
+    // vector registers, which the compiler otherwise fills with them and spills
+    // the lanes' walk state for (at 96 registers 73 spilled, weighted; now 80
+    // and none, unweighted)
+    const uint32_t wv = uni(threadIdx.x / WAVE);
+    HubLds &L = lds[wv];
+    Slot *sl = slots[wv];
     const int l = lane_id();
     const uint32_t total = S.total();
     const uint32_t tw = E.t_wave < E.g.d_rule ? E.t_wave : E.g.d_rule;
@@ -1617,7 +1676,7 @@ __global__ __launch_bounds__(PBLOCK, 5) void k_persistent(Exec E_arg, Src S)
     // shrink with what is left (guided self-scheduling, down to one walk), so
     // that no wavefront holds unstarted walks while others have run dry.
     const uint32_t nwaves = gridDim.x * (PBLOCK / WAVE);
-    const uint32_t wid = blockIdx.x * (PBLOCK / WAVE) + threadIdx.x / WAVE;
+    const uint32_t wid = blockIdx.x * (PBLOCK / WAVE) + wv;
     const uint32_t lanes = walk_lanes(E, total / nwaves);
     const uint32_t share0 = first_share(E, total / nwaves, lanes);
     const uint32_t given = share0 ? nwaves * share0 : total;  // walks given out by index
@@ -1631,7 +1690,7 @@ __global__ __launch_bounds__(PBLOCK, 5) void k_persistent(Exec E_arg, Src S)
     for (;;) {
         // refill and thread class: the lane's own walk
         {
-            Slot q = sl[l];
+            const Slot q = sl[l];
             WS st;
             bool live = q.flags & SL_LIVE;
             bool pend = q.flags & SL_PEND;
@@ -1711,10 +1770,15 @@ __global__ __launch_bounds__(PBLOCK, 5) void k_persistent(Exec E_arg, Src S)
                     cap = SL_CAP;
                 }
             }
-            if (live) flush<WALKS>(J, st.i, st.s, cb);
-            if (live) ws_to_slot(st, SL_LIVE | (pend ? SL_PEND : 0) | cap, k, q);
-            else q.flags = 0;
-            sl[l] = q;
+            // (a lane without a walk keeps nothing of its slot alive until here)
+            if (live) {
+                flush<WALKS>(J, st.i, st.s, cb);
+                Slot r;
+                ws_to_slot(st, SL_LIVE | (pend ? SL_PEND : 0) | cap, k, r);
+                sl[l] = r;
+            } else {
+                sl[l].flags = 0;
+            }
         }
         wave_lds_sync();
         // wave and hub classes, one pending walk at a time, state in scalars
@@ -2007,7 +2071,7 @@ __global__ void k_zero(uint32_t *p, uint32_t n)
 // ---------------------------------------------------------------- host
 struct DevInfo {
     int cus = 0;
-    int occ = 0;
+    int occ[3] = {};  // workgroups of the persistent kernel per CU, by Kind
 };
 
 DevInfo &dev_info(int dev)
@@ -2018,10 +2082,14 @@ DevInfo &dev_info(int dev)
         hipDeviceProp_t prop;
         if (hipGetDeviceProperties(&prop, dev) == hipSuccess) d.cus = prop.multiProcessorCount;
         if (d.cus <= 0) d.cus = 256;
-        int b = 0;
-        (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, (const void *)k_persistent<OneJob, true, true, WEIGHTED>,
-                                                           PBLOCK, 0);
-        d.occ = b > 0 ? b : 2;
+        const void *kernels[3] = {(const void *)k_persistent<OneJob, true, true, PLAIN_ENTRIES>,
+                                  (const void *)k_persistent<OneJob, true, true, WIDE_ENTRIES>,
+                                  (const void *)k_persistent<OneJob, true, true, WEIGHTED>};
+        for (int k = 0; k < 3; ++k) {
+            int b = 0;
+            (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, kernels[k], PBLOCK, 0);
+            d.occ[k] = b > 0 ? b : 2;
+        }
     }
     return d;
 }
@@ -2035,11 +2103,11 @@ size_t plain_ws(uint32_t n_starts, uint32_t L)
     return c.total();
 }
 
-uint32_t persistent_blocks(const n2v_exec_opts &o, int dev, uint64_t walks, bool few_hubs)
+uint32_t persistent_blocks(const n2v_exec_opts &o, int dev, Kind K, uint64_t walks, bool few_hubs)
 {
     DevInfo &d = dev_info(dev);
-    uint32_t per_cu = o.waves_per_cu ? (o.waves_per_cu + (PBLOCK / WAVE) - 1) / (PBLOCK / WAVE) : (uint32_t)d.occ;
-    if (per_cu > (uint32_t)d.occ) per_cu = d.occ;
+    uint32_t per_cu = o.waves_per_cu ? (o.waves_per_cu + (PBLOCK / WAVE) - 1) / (PBLOCK / WAVE) : (uint32_t)d.occ[K];
+    if (per_cu > (uint32_t)d.occ[K]) per_cu = d.occ[K];
     if (per_cu < 1) per_cu = 1;
     uint64_t blocks = (uint64_t)d.cus * per_cu;
     // Small jobs: down to a wavefront per walk.  Past a walk per wavefront, a
@@ -2059,14 +2127,14 @@ template <bool W, bool C>
 int launch_persistent(const Exec &E_opts, const OneJob &S, const n2v_exec_opts &o, int dev, hipStream_t st)
 {
     Exec E = E_opts;
-    const uint32_t blocks = persistent_blocks(o, dev, S.n, E.thread_iters > 4);
+    const Kind K = kind_of(E);
+    const uint32_t blocks = persistent_blocks(o, dev, K, S.n, E.thread_iters > 4);
     // A walk alone on its wavefront lasts as long as its chain of attempts:
     // the wavefront makes 64 of a move at once (1000 walks of 40 moves on
     // ER-20: 139 -> 75 us).  Not where hubs are common, whose lines the other
     // 60 attempts' reads push out (100 walks at scale 16: 165 against 194 us).
     if (E.lane_div == 1 && S.n <= blocks * (PBLOCK / WAVE)) E.t_wave = 0;
     hipLaunchKernelGGL(k_zero, dim3(1), dim3(64), 0, st, S.cur, 1u);
-    const Kind K = kind_of(E);
     auto kernel = K == WEIGHTED       ? k_persistent<OneJob, W, C, WEIGHTED>
                   : K == WIDE_ENTRIES ? k_persistent<OneJob, W, C, WIDE_ENTRIES>
                                       : k_persistent<OneJob, W, C, PLAIN_ENTRIES>;
@@ -2367,10 +2435,10 @@ int launch_plain_replayed(const n2v_graph *g, const Exec &E, const OneJob &S, vo
     return N2V_OK;
 }
 
-uint32_t full_grid_blocks(int dev)
+uint32_t full_grid_blocks(const Exec &E, int dev)
 {
     DevInfo &d = dev_info(dev);
-    return (uint32_t)d.cus * (uint32_t)d.occ;
+    return (uint32_t)d.cus * (uint32_t)d.occ[kind_of(E)];
 }
 
 int launch_job_table(const Exec &E, const TableHdr *hdr, uint32_t blocks, hipStream_t st)
