@@ -192,11 +192,11 @@ int n2v_walk_workspace(const n2v_graph *g, uint32_t n_starts, uint32_t L,
  * modulo 2^64), H = r0*2^32 + r1 of Philox(key = seed; ctr = (walk id mod
  * 2^32, c, x, 3)).  Counts accumulate: zero them before the first chunk.
  * `opts` may be NULL (defaults); `ws` may be NULL when the query says 0.
- * The plain form (N2V_MODE_PLAIN) is one superstep of two kernels per move
- * (Algorithm 1).  A plain call whose every argument (pointers, sizes, options,
+ * The plain form (N2V_MODE_PLAIN) is one superstep per move (Algorithm 1): two
+ * kernels, or one where hub moves are rare and the walks few.  A plain call whose every argument (pointers, sizes, options,
  * seed) equals that of one of the graph's last 8 distinct plain calls is
  * recorded into a HIP graph on its second occurrence and replayed from then
- * on: one graph launch instead of 2L+2 kernel launches, same results, and the
+ * on: one graph launch instead of up to 2L+2 kernel launches, same results, and the
  * buffers' contents may change between calls.  Recording allocates the
  * graph's host and device memory; calls enqueued on a stream that is being
  * captured launch their kernels directly. */

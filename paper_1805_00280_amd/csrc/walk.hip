@@ -329,24 +329,19 @@ __device__ __forceinline__ bool attempt(const Exec &E, const JobCtx &J, const WS
     return a.u < (is_member(E, st, b.x) ? A_COM : J.A_out) * a.w;
 }
 
-// Thread class: attempts in order until one accepts (false after a_cap, or
-// after the first kmax attempts).
-__device__ bool thread_reject(const Exec &E, const JobCtx &J, const WS &st, uint32_t &j_out, Nb &b,
-                              uint32_t kmax = 0xFFFFFFFFu)
+// Thread class: attempts in order until one accepts (false after a_cap).
+__device__ bool thread_reject(const Exec &E, const JobCtx &J, const WS &st, uint32_t &j_out, Nb &b)
 {
-    const uint32_t n = kmax < E.g.a_cap ? kmax : E.g.a_cap;
-    for (uint32_t k = 0; k < n; ++k)
+    for (uint32_t k = 0; k < E.g.a_cap; ++k)
         if (attempt(E, J, st, k, j_out, b)) return true;
     return false;
 }
 
-// Wave class: lanes take attempts k0 + lane (from attempt kfrom on, the
-// earlier ones having rejected); the lowest accepting one wins.
-__device__ bool wave_reject(const Exec &E, const JobCtx &J, const WS &st_in, uint32_t &j_out, Nb &b_out,
-                            uint32_t kfrom = 0)
+// Wave class: lanes take attempts k0 + lane; the lowest accepting one wins.
+__device__ bool wave_reject(const Exec &E, const JobCtx &J, const WS &st_in, uint32_t &j_out, Nb &b_out)
 {
     const WS st = uniform_ws(st_in);
-    for (uint32_t k0 = kfrom; k0 < E.g.a_cap; k0 += WAVE) {
+    for (uint32_t k0 = 0; k0 < E.g.a_cap; k0 += WAVE) {
         const uint32_t k = k0 + lane_id();
         uint32_t j = 0;
         Nb b = {};
@@ -1901,82 +1896,114 @@ __device__ __forceinline__ void plain_finish(const JobCtx &J, WS &st, uint32_t j
     if (!wave || lane_id() == 0) state[st.i] = make_uint4(end ? SENT : b.x, st.v, b.rev, j);
 }
 
-// Rejection attempts a lane of the plain thread kernel makes alone when a
-// superstep is small; its wavefront then takes the attempts that follow, 64
-// at a time, so that the superstep does not wait for one lane's long chain.
-// (A large superstep hides such chains behind other wavefronts.)
-constexpr uint32_t PLAIN_LANE_ATTEMPTS = 16;
+// Rejection by groups of GRP lanes, each group with a walk of its own: lane g
+// of a group takes attempts g, g + GRP, ...; the lowest accepting one wins.
+// False after a_cap attempts.
+template <int GRP>
+__device__ __forceinline__ bool group_reject(const Exec &E, const JobCtx &J, const WS &st, bool active, uint32_t &j_out,
+                                             Nb &b_out)
+{
+    const int l = lane_id(), lead = l & ~(GRP - 1);
+    bool done = false;
+    for (uint32_t k0 = 0;; k0 += GRP) {
+        const bool go = active && !done && k0 < E.g.a_cap;
+        if (ballot(go) == 0) break;
+        const uint32_t k = k0 + (uint32_t)(l - lead);
+        uint32_t j = 0;
+        Nb b = {};
+        const bool acc = go && k < E.g.a_cap && attempt(E, J, st, k, j, b);
+        const uint64_t m = (ballot(acc) >> lead) & (GRP == WAVE ? ~0ull : (1ull << (GRP & (WAVE - 1))) - 1ull);
+        const int src = lead + (m ? first_lane(m) : 0);
+        j = shfl32(j, src);
+        b.x = shfl32(b.x, src);
+        b.rev = shfl32(b.rev, src);
+        if (go && m) {
+            j_out = j;
+            b_out = b;
+            done = true;
+        }
+    }
+    return done;
+}
 
-// Hub moves are queued for k_plain_hub: dense moves at degree > t_wg at the
-// top of hubq (growing down, one workgroup each), all others at the bottom.
-template <bool WALKS, bool COUNTS, Kind K, bool COOP>
+// One superstep.  GRP lanes make a walk's rejection attempts (a superstep
+// lasts as long as its slowest chain, so a small one spreads each chain over
+// lanes that would idle).  FUSED: the wavefront also makes its walks' hub and
+// capped moves, and the superstep is this one launch.  Otherwise they are
+// queued for k_plain_hub: dense moves at degree > t_wg at the top of hubq
+// (growing down, one workgroup each), all others at the bottom.
+template <bool WALKS, bool COUNTS, Kind K, int GRP, bool FUSED>
 __global__ __launch_bounds__(256) void k_plain_step(Exec E_arg, OneJob S, uint32_t s, uint4 *__restrict__ state,
                                                     uint32_t *__restrict__ hubq, uint32_t *__restrict__ hubn,
                                                     uint32_t *__restrict__ bign)
 {
     const Exec E = exec_for<K>(E_arg);
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    const uint64_t tid = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const uint32_t i = (uint32_t)(tid / GRP);
+    const bool lead = GRP == 1 || lane_id() % GRP == 0;
     uint64_t csum = 0;
-    bool push = false, big = false, pend = false;
+    bool push = false, big = false, rej = false;
     uint32_t item = 0;
     WS st;
-    if (i < S.n) {
-        if (plain_load(E, state[i], i, s, st)) {
-            if (st.vd == 0) {
-                // the previous move reached a dead end: the rest of the row is N2V_SENT
+    if (tid / GRP < S.n && plain_load(E, state[i], i, s, st)) {
+        if (st.vd == 0) {
+            // the previous move reached a dead end: the rest of the row is N2V_SENT
+            if (lead) {
                 fill_tail_lane<WALKS>(S.c, i, s);
                 state[i].x = SENT;
-            } else if (st.vd > E.g.d_rule) {
-                item = i;
-                // workgroups pay off on full merges: with sketches, only moves
-                // whose sketch looks unknown (first count still 0) go to them
-                big = s > 0 && st.vd > E.t_wg && !use_sparse(E, st) && !approx_first_order(E, S.c, st) &&
-                      !(E.g.memo && st.pos_t != SENT && st.vd >= E.g.memo_min &&
-                        st.vd <= MEMO_MAX_DEG && sketch_row(E, st, st.pos_t)[0] != 0);
-                push = !big;
-            } else {
-                uint32_t j;
-                Nb b;
-                if (thread_reject(E, S.c, st, j, b, COOP ? PLAIN_LANE_ATTEMPTS : 0xFFFFFFFFu)) {
-                    plain_finish<WALKS, COUNTS>(S.c, st, j, b, state, csum, false);
-                } else if (COOP) {
-                    pend = true;
-                } else {
-                    push = true;  // every attempt rejected: the inverse CDF of attempt a_cap
-                    item = i | 0x80000000u;
-                }
             }
+        } else if (st.vd > E.g.d_rule) {
+            item = i;
+            // workgroups pay off on full merges: with sketches, only moves
+            // whose sketch looks unknown (first count still 0) go to them
+            big = !FUSED && s > 0 && st.vd > E.t_wg && !use_sparse(E, st) && !approx_first_order(E, S.c, st) &&
+                  !(E.g.memo && st.pos_t != SENT && st.vd >= E.g.memo_min && st.vd <= MEMO_MAX_DEG &&
+                    sketch_row(E, st, st.pos_t)[0] != 0);
+            push = !big;
+        } else {
+            rej = true;
         }
     }
-    if constexpr (COOP) {
-        for (uint64_t pm = ballot(pend); pm; pm &= pm - 1) {
+    {
+        uint32_t j;
+        Nb b;
+        const bool done = GRP == 1 ? rej && thread_reject(E, S.c, st, j, b) : group_reject<GRP>(E, S.c, st, rej, j, b);
+        if (rej && !done) {
+            push = true;  // every attempt rejected: the inverse CDF of attempt a_cap
+            item = i | 0x80000000u;
+        }
+        if (done && lead) plain_finish<WALKS, COUNTS>(S.c, st, j, b, state, csum, false);
+    }
+    push = push && lead;
+    big = big && lead;
+    if constexpr (FUSED) {
+        __shared__ HubLds lds[256 / WAVE];
+        HubLds &L = lds[uni(threadIdx.x / WAVE)];
+        for (uint64_t pm = ballot(push); pm; pm &= pm - 1) {
             const int o = first_lane(pm);
             WS w = bcast(st, o);
-            uint32_t j;
-            Nb b;
-            if (wave_reject(E, S.c, w, j, b, PLAIN_LANE_ATTEMPTS)) {
-                plain_finish<WALKS, COUNTS>(S.c, w, j, b, state, csum, true);
-            } else if (lane_id() == o) {
-                push = true;
-                item = i | 0x80000000u;
-            }
+            const uint32_t kidx = lane_val(item, o) & 0x80000000u ? E.g.a_cap : 0u;
+            uint32_t xj;
+            const uint32_t j = wave_inverse_cdf(E, S.c, w, kidx, L, xj);
+            plain_finish<WALKS, COUNTS>(S.c, w, j, resolve(E, w, j), state, csum, true);
         }
-    }
-    const uint64_t m = ballot(push);
-    if (m) {
-        uint32_t base = 0;
-        const int lead = first_lane(m);
-        if (lane_id() == lead) base = atomicAdd(hubn, (uint32_t)__popcll(m));
-        base = shfl32(base, lead);
-        if (push) hubq[base + __popcll(m & lanemask_lt())] = item;
-    }
-    const uint64_t mb = ballot(big);
-    if (mb) {
-        uint32_t base = 0;
-        const int lead = first_lane(mb);
-        if (lane_id() == lead) base = atomicAdd(bign, (uint32_t)__popcll(mb));
-        base = shfl32(base, lead);
-        if (big) hubq[S.n - 1 - (base + __popcll(mb & lanemask_lt()))] = item;
+    } else {
+        const uint64_t m = ballot(push);
+        if (m) {
+            uint32_t base = 0;
+            const int first = first_lane(m);
+            if (lane_id() == first) base = atomicAdd(hubn, (uint32_t)__popcll(m));
+            base = shfl32(base, first);
+            if (push) hubq[base + __popcll(m & lanemask_lt())] = item;
+        }
+        const uint64_t mb = ballot(big);
+        if (mb) {
+            uint32_t base = 0;
+            const int first = first_lane(mb);
+            if (lane_id() == first) base = atomicAdd(bign, (uint32_t)__popcll(mb));
+            base = shfl32(base, first);
+            if (big) hubq[S.n - 1 - (base + __popcll(mb & lanemask_lt()))] = item;
+        }
     }
     if (COUNTS) {
         csum = wave_sum(csum);
@@ -2160,19 +2187,29 @@ int launch_plain_kind(const Exec &E, const OneJob &S, void *ws, int dev, hipStre
     N2V_HIP(hipGetLastError());
     DevInfo &d = dev_info(dev);
     const uint32_t hub_blocks = (uint32_t)d.cus * 8;
-    // the thread kernel lasts as long as its slowest lane's chain of dependent
-    // reads: a small superstep is spread over every CU, one wavefront per
-    // block, and its wavefronts finish their lanes' long rejection chains
-    // together
-    const uint32_t tpb = S.n < (uint32_t)d.cus * 1024u ? 64u : 256u;
-    const uint32_t sblocks = (S.n + tpb - 1) / tpb;
+    // A superstep lasts as long as its slowest chain of dependent reads: while
+    // the walks fill no more than the chip's 32 wavefronts per CU with 64 (8, 4)
+    // lanes each, as many take a walk's attempts.  Where hub moves are rare
+    // those wavefronts make them too, and the superstep is one launch (40,960
+    // walks of 80 moves at scale 12: 2.33 -> 1.35 ms; 10,000 of 40 on ER-18 0.70
+    // -> 0.28 ms).  Where they are common they are queued, each wavefront's with
+    // one atomic on the queue's counter, so groups pay off only for fewer
+    // walks: 1 / 4 / 8 / 64 lanes measured 2.98 / 2.62 / 2.84 / 3.40 ms for
+    // 20,000 walks at scale 16, 9.1 / 10.2 / 11.6 / 14.5 ms for 100,000, 2.47 /
+    // 1.87 / 1.77 / 1.84 ms for 3000.
+    const uint32_t slots = (uint32_t)d.cus * 32u * WAVE;
+    const bool few_hubs = E.lane_div == 1;
+    const int grp = few_hubs ? (S.n <= slots / 64 ? 64 : (S.n <= slots / 8 ? 8 : (S.n <= slots / 2 ? 4 : 1)))
+                             : (S.n <= slots / 64 ? 8 : (S.n <= slots / 16 ? 4 : 1));
+    const bool fused = grp >= 8 && few_hubs;
+    auto step = grp == 64  ? k_plain_step<W, C, K, 64, true>
+                : grp == 8 ? (fused ? k_plain_step<W, C, K, 8, true> : k_plain_step<W, C, K, 8, false>)
+                : grp == 4 ? k_plain_step<W, C, K, 4, false>
+                           : k_plain_step<W, C, K, 1, false>;
+    const uint32_t sblocks = (uint32_t)(((uint64_t)S.n * grp + 255) / 256);
     for (uint32_t s = 0; s < S.c.L; ++s) {
-        if (tpb == 64)
-            hipLaunchKernelGGL((k_plain_step<W, C, K, true>), dim3(sblocks), dim3(tpb), 0, st, E, S, s, state, hubq,
-                               hubn + s, bign + s);
-        else
-            hipLaunchKernelGGL((k_plain_step<W, C, K, false>), dim3(sblocks), dim3(tpb), 0, st, E, S, s, state, hubq,
-                               hubn + s, bign + s);
+        hipLaunchKernelGGL(step, dim3(sblocks), dim3(256), 0, st, E, S, s, state, hubq, hubn + s, bign + s);
+        if (fused) continue;
         hipLaunchKernelGGL((k_plain_hub<W, C, K>), dim3(hub_blocks), dim3(HBLOCK), 0, st, E, S, s, state, hubq,
                            (const uint32_t *)(hubn + s), hubd + s, (const uint32_t *)(bign + s), bigd + s);
     }

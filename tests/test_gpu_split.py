@@ -80,3 +80,19 @@ def test_large_graph_of_short_rows(p, q):
     for mode in (P.MODE_PERSISTENT, P.MODE_PLAIN):
         got = gpu_walk(g2, starts, 15, p, q, 77, mode=mode)
         assert first_mismatch(got, want) is None, (mode, first_mismatch(got, want))
+
+
+@pytest.mark.parametrize("d_rule,a_cap", [(1024, 1024), (100, 1024), (12, 3)])  # few hub moves, many, and capped ones
+def test_plain_supersteps_of_every_size(d_rule, a_cap):
+    # 1, 4, 8 or 64 lanes make a walk's attempts, by the number of walks; hub
+    # and capped moves in the same launch or queued
+    torch_cuda()
+    og = oracle_rmat(10, 8, 0.57, 0.19, 0.19, 6, False)
+    g = gpu_graph_from_oracle(og, d_rule=d_rule, a_cap=a_cap)
+    for n in (1, 7, 65, 8192, 8193, 32_769, 65_537, 262_145):
+        say(f"[plain] d_rule={d_rule} walks={n}")
+        starts = (np.arange(n, dtype=np.uint64) * 5 % og.n).astype(np.uint32)
+        L = 6 if n < 100_000 else 3
+        want = oracle_walk(og, starts, L, 0.25, 2.0, 12, d_rule=d_rule, a_cap=a_cap)
+        got = gpu_walk(g, starts, L, 0.25, 2.0, 12, mode=P.MODE_PLAIN)
+        assert first_mismatch(got, want) is None, (n, first_mismatch(got, want))
