@@ -265,6 +265,7 @@ struct n2v_server {
                 jr.c.A_ret = r.A_ret;
                 jr.c.A_out = r.A_out;
                 jr.c.approx_t = r.approx_t;
+                jr.c.hist = 0;
                 jr.starts = r.d_starts + r.next;
                 jr.n = k;
                 h->jstart[nj] = total;

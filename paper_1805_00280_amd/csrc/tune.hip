@@ -77,6 +77,7 @@ extern "C" int n2v_autotune(n2v_graph *g, uint32_t n_walks, uint32_t L, float p,
     c.A_ret = A_ret;
     c.A_out = A_out;
     c.approx_t = 0;
+    c.hist = 0;
 
     // events released on every return path
     struct Events {

@@ -139,12 +139,21 @@ __device__ __forceinline__ uint32_t amax3(const JobCtx &J)
     return m > J.A_out ? m : J.A_out;
 }
 
+// Visit counters of a small graph in LDS.  Atomics on one address of memory
+// take about 25 ns each, so the hubs' counters bounded a launch on few
+// vertices (14,548 walks of 73 moves on 2048 vertices: 877 against 303 us; 40,960 on 4096:
+// 2.49 against 1.00 ms); with up to
+// this many, a workgroup counts in LDS and adds its counts at its end.
+constexpr uint32_t HIST_MAX = 4096;
+extern __shared__ uint32_t visit_hist[];
+
 template <bool WALKS, bool COUNTS>
 __device__ __forceinline__ void emit(const JobCtx &J, uint32_t i, uint32_t col, uint32_t x, uint64_t &csum)
 {
     if (WALKS) J.out[(uint64_t)i * (J.L + 1) + col] = x;
     if (COUNTS) {
-        atomicAdd(&J.cnt[x], 1u);
+        if (J.hist) atomicAdd(&visit_hist[x], 1u);
+        else atomicAdd(&J.cnt[x], 1u);
         const R4 h = philox(J.k0, J.k1, J.wbase + i, col, x, 3u);
         csum += join64(h.x, h.y);
     }
@@ -1682,6 +1691,10 @@ __global__ __launch_bounds__(PBLOCK, K == PLAIN_ENTRIES ? 6 : 5) void k_persiste
     bool exhausted = given >= total;
     uint64_t csum = 0;
     sl[l].flags = 0;
+    if (COUNTS && S.ctx(0).hist) {
+        for (uint32_t x = threadIdx.x; x < E.g.n; x += PBLOCK) visit_hist[x] = 0;
+        __syncthreads();
+    }
     for (;;) {
         // refill and thread class: the lane's own walk
         {
@@ -1842,6 +1855,13 @@ __global__ __launch_bounds__(PBLOCK, K == PLAIN_ENTRIES ? 6 : 5) void k_persiste
     if (COUNTS) {
         csum = wave_sum(csum);
         if (l == 0 && csum) atomicAdd(S.ctx(0).checksum, (unsigned long long)csum);
+        if (S.ctx(0).hist) {
+            __syncthreads();  // every wavefront comes here, once the walks have run out
+            for (uint32_t x = threadIdx.x; x < E.g.n; x += PBLOCK) {
+                const uint32_t c = visit_hist[x];
+                if (c) atomicAdd(S.ctx(0).cnt + x, c);
+            }
+        }
     }
 }
 
@@ -2006,8 +2026,16 @@ __global__ __launch_bounds__(256) void k_plain_step(Exec E_arg, OneJob S, uint32
         }
     }
     if (COUNTS) {
+        // one atomic per workgroup: they all meet at one address
+        __shared__ unsigned long long part[256 / WAVE];
         csum = wave_sum(csum);
-        if (lane_id() == 0 && csum) atomicAdd(S.c.checksum, (unsigned long long)csum);
+        if (lane_id() == 0) part[threadIdx.x / WAVE] = csum;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            unsigned long long t = 0;
+            for (int w = 0; w < 256 / WAVE; ++w) t += part[w];
+            if (t) atomicAdd(S.c.checksum, t);
+        }
     }
 }
 
@@ -2151,11 +2179,17 @@ uint32_t persistent_blocks(const n2v_exec_opts &o, int dev, Kind K, uint64_t wal
 }
 
 template <bool W, bool C>
-int launch_persistent(const Exec &E_opts, const OneJob &S, const n2v_exec_opts &o, int dev, hipStream_t st)
+int launch_persistent(const Exec &E_opts, const OneJob &S_opts, const n2v_exec_opts &o, int dev, hipStream_t st)
 {
     Exec E = E_opts;
+    OneJob S = S_opts;
     const Kind K = kind_of(E);
-    const uint32_t blocks = persistent_blocks(o, dev, K, S.n, E.thread_iters > 4);
+    uint32_t blocks = persistent_blocks(o, dev, K, S.n, E.thread_iters > 4);
+    // three workgroups per CU with their counters (each adds up to n of them at
+    // its end, so not for few walks)
+    S.c.hist = C && E.g.n <= HIST_MAX && (uint64_t)S.n * S.c.L >= 64ull * E.g.n;
+    if (S.c.hist) blocks = std::min(blocks, 3u * (uint32_t)dev_info(dev).cus);
+    const size_t lds = S.c.hist ? E.g.n * sizeof(uint32_t) : 0;
     // A walk alone on its wavefront lasts as long as its chain of attempts:
     // the wavefront makes 64 of a move at once (1000 walks of 40 moves on
     // ER-20: 139 -> 75 us).  Not where hubs are common, whose lines the other
@@ -2165,7 +2199,7 @@ int launch_persistent(const Exec &E_opts, const OneJob &S, const n2v_exec_opts &
     auto kernel = K == WEIGHTED       ? k_persistent<OneJob, W, C, WEIGHTED>
                   : K == WIDE_ENTRIES ? k_persistent<OneJob, W, C, WIDE_ENTRIES>
                                       : k_persistent<OneJob, W, C, PLAIN_ENTRIES>;
-    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(PBLOCK), 0, st, E, S);
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(PBLOCK), lds, st, E, S);
     N2V_HIP(hipGetLastError());
     return N2V_OK;
 }
@@ -2199,12 +2233,15 @@ int launch_plain_kind(const Exec &E, const OneJob &S, void *ws, int dev, hipStre
     // 1.87 / 1.77 / 1.84 ms for 3000.
     const uint32_t slots = (uint32_t)d.cus * 32u * WAVE;
     const bool few_hubs = E.lane_div == 1;
-    const int grp = few_hubs ? (S.n <= slots / 64 ? 64 : (S.n <= slots / 8 ? 8 : (S.n <= slots / 2 ? 4 : 1)))
-                             : (S.n <= slots / 64 ? 8 : (S.n <= slots / 16 ? 4 : 1));
-    const bool fused = grp >= 8 && few_hubs;
+    int grp = few_hubs ? (S.n <= slots / 64 ? 64 : (S.n <= slots / 8 ? 8 : (S.n <= slots / 2 ? 4 : 1)))
+                       : (S.n <= slots / 64 ? 8 : (S.n <= slots / 16 ? 4 : 1));
+    // counting adds each workgroup's checksum at one address: no more of them
+    // than a quarter of the walks' wavefronts need
+    if (C && grp > 4) grp = S.n <= slots / 512 ? 8 : 4;
+    const bool fused = grp >= 4 && few_hubs;
     auto step = grp == 64  ? k_plain_step<W, C, K, 64, true>
                 : grp == 8 ? (fused ? k_plain_step<W, C, K, 8, true> : k_plain_step<W, C, K, 8, false>)
-                : grp == 4 ? k_plain_step<W, C, K, 4, false>
+                : grp == 4 ? (fused ? k_plain_step<W, C, K, 4, true> : k_plain_step<W, C, K, 4, false>)
                            : k_plain_step<W, C, K, 1, false>;
     const uint32_t sblocks = (uint32_t)(((uint64_t)S.n * grp + 255) / 256);
     for (uint32_t s = 0; s < S.c.L; ++s) {
@@ -2578,6 +2615,7 @@ int walk_impl(const n2v_graph *g, const uint32_t *starts, uint32_t n_starts, uin
     S.c.A_ret = A_ret;
     S.c.A_out = A_out;
     S.c.approx_t = approx_t;
+    S.c.hist = 0;
     S.starts = starts;
     S.n = n_starts;
     S.cur = nullptr;
