@@ -15,14 +15,14 @@ FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-function", "-Wno-unused-result",
 ]
-# The persistent walk kernel is held to 96 VGPRs (five wavefronts per SIMD).
-# The compiler hoists the hub path's lane constants out of the walk loop, where
-# they push the lanes' walk state into scratch: 77 spilled registers unweighted
-# (121 weighted), stored and reloaded on every rejection move.  Sinking them
-# back leaves 0 (67): ER-22 29.2 -> 24.2 ms, WeC-22 72.9 -> 67.7 ms, FN-Approx
-# on Skew-5 172.6 -> 158.0 ms, weighted scale 20 278 -> 252 ms.  The Skip-gram
-# kernel spills nothing and is 5% slower with it, so it is a flag of walk.hip
-# alone.
+# The persistent walk kernel is held to 80 VGPRs (six wavefronts per SIMD;
+# weighted 96, five).  The compiler hoists the hub path's lane constants out of
+# the walk loop, where they push the lanes' walk state into scratch (86 spilled
+# registers, weighted 166), stored and reloaded on every rejection move.
+# Sinking them back leaves none (3).  When the flag came (one kernel of 96
+# registers): ER-22 29.2 -> 24.2 ms, WeC-22 72.9 -> 67.7 ms, FN-Approx on Skew-5
+# 172.6 -> 158.0 ms, weighted scale 20 278 -> 252 ms.  The Skip-gram kernel
+# spills nothing and is 5% slower with it, so it is a flag of walk.hip alone.
 SOURCE_FLAGS = {"walk.hip": ["-mllvm", "-sink-insts-to-avoid-spills=1"]}
 
 
