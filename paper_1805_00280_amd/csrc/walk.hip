@@ -2158,10 +2158,11 @@ size_t plain_ws(uint32_t n_starts, uint32_t L)
     return c.total();
 }
 
-uint32_t persistent_blocks(const n2v_exec_opts &o, int dev, Kind K, uint64_t walks, bool few_hubs)
+uint32_t persistent_blocks(const n2v_exec_opts &o, int dev, Kind K, uint32_t wg_cap, uint64_t walks, bool few_hubs)
 {
     DevInfo &d = dev_info(dev);
     uint32_t per_cu = o.waves_per_cu ? (o.waves_per_cu + (PBLOCK / WAVE) - 1) / (PBLOCK / WAVE) : (uint32_t)d.occ[K];
+    if (!o.waves_per_cu && per_cu > wg_cap) per_cu = wg_cap;
     if (per_cu > (uint32_t)d.occ[K]) per_cu = d.occ[K];
     if (per_cu < 1) per_cu = 1;
     uint64_t blocks = (uint64_t)d.cus * per_cu;
@@ -2184,7 +2185,7 @@ int launch_persistent(const Exec &E_opts, const OneJob &S_opts, const n2v_exec_o
     Exec E = E_opts;
     OneJob S = S_opts;
     const Kind K = kind_of(E);
-    uint32_t blocks = persistent_blocks(o, dev, K, S.n, E.thread_iters > 4);
+    uint32_t blocks = persistent_blocks(o, dev, K, E.wg_cap, S.n, E.thread_iters > 4);
     // three workgroups per CU with their counters (each adds up to n of them at
     // its end, so not for few walks)
     S.c.hist = C && E.g.n <= HIST_MAX && (uint64_t)S.n * S.c.L >= 64ull * E.g.n;
@@ -2390,6 +2391,16 @@ void make_exec(const n2v_graph *g, const n2v_exec_opts &o, Exec *E)
     // 1 up to 10% of the entries in hub rows, 8 from 40% (see walk_lanes)
     const uint64_t twentieths = m ? he * 20 / m : 0;
     E->lane_div = twentieths < 1 ? 1u : (twentieths > 8 ? 8u : (uint32_t)twentieths);
+    // Workgroups per CU: all that fit, but five where the hub rows alone exceed
+    // twice the 256 MB last-level cache: more merges at once then read more of
+    // their lines from memory (scale 24 skewed: L2 hit rate 28%, 290 G line
+    // reads; before the sixth 46%, 218 G).  Five against six, one walk per
+    // vertex: 270 M hub entries (scale 24 skewed) 2.77 / 3.35 s, without
+    // sketches 2.60 / 3.21 s (a quarter of the walks), 236 M (scale 24) 1.99 /
+    // 2.32 s, 141 M (scale 23 skewed) 1.11 / 1.20 s; but 84 M (Skew-5,
+    // FN-Approx) 97.6 / 88.5 ms, 50 M (scale 22 skewed) 386 / 353 ms, 47 M
+    // (scale 22) 334 / 305 ms.
+    E->wg_cap = he >= 1ull << 27 ? 5u : 16u;
 }
 
 PlainKey plain_key(const Exec &E, const OneJob &S, const void *ws, uint32_t hub_blocks, bool W, bool C)
@@ -2419,6 +2430,7 @@ PlainKey plain_key(const Exec &E, const OneJob &S, const void *ws, uint32_t hub_
     k.put2(E.sparse_ratio, E.t_wg);
     k.put2(E.search_ratio, hub_blocks);
     k.put2(E.thread_iters, E.lane_div);
+    k.put(E.wg_cap);
     k.put(E.cursor);
     k.put(S.c.out);
     k.put(S.c.cnt);
@@ -2512,7 +2524,7 @@ int launch_plain_replayed(const n2v_graph *g, const Exec &E, const OneJob &S, vo
 uint32_t full_grid_blocks(const Exec &E, int dev)
 {
     DevInfo &d = dev_info(dev);
-    return (uint32_t)d.cus * (uint32_t)d.occ[kind_of(E)];
+    return (uint32_t)d.cus * std::min((uint32_t)d.occ[kind_of(E)], E.wg_cap);
 }
 
 int launch_job_table(const Exec &E, const TableHdr *hdr, uint32_t blocks, hipStream_t st)

@@ -17,6 +17,7 @@ struct Exec {
     uint32_t search_ratio;  // dense merges search N(v) in N(t) when N(t)'s range is longer by more
     uint32_t thread_iters;  // persistent form: attempts per lane before the wave serves pending walks
     uint32_t lane_div;      // persistent form: a wavefront starts one in lane_div of its walks at once
+    uint32_t wg_cap;        // persistent form: most workgroups per CU
     uint32_t *cursor;       // walk counter of a single-job launch (taken per launch, zeroed before it)
 };
 
