@@ -30,6 +30,7 @@
 #include <new>
 
 #include "prims.hpp"
+#include "split.hpp"
 #include "walk.hpp"
 
 namespace n2v {
@@ -1565,7 +1566,7 @@ struct JobTable {
 
 // ---------------------------------------------------------- persistent
 constexpr int PBLOCK = 256;
-constexpr int POOL = 256;  // most walks a wavefront claims per atomic
+static_assert(SPLIT_LANES == WAVE && SPLIT_WAVES == PBLOCK / WAVE, "split.hpp's wavefronts and workgroups");
 
 // Walk slot of one lane, kept in LDS between the thread and wave phases so
 // that neither phase holds the other's registers.
@@ -1628,29 +1629,6 @@ __device__ __forceinline__ Exec exec_for(const Exec &E)
     return e;
 }
 
-// Lanes of a wavefront that take walks.  Where hub moves are common a
-// wavefront makes them one after the other: the walks that share it wait for
-// each other, and a wavefront that meets many holds up the launch's end.  So
-// the more of the entries lie in hub rows (lane_div), the smaller a part of
-// its walks a wavefront starts at once (eight where it has eight); the rest go
-// to whoever is free.  Measured with all walks started by index / half / a
-// quarter / an eighth of them: 48 walks per wavefront at scale 18 without
-// sketches 34.8 / 34.2 / 29.2 / 28.6 ms, 8 per wavefront at scale 16 1.41 /
-// 1.38 / 1.43 / 1.61 ms.
-__device__ __forceinline__ uint32_t walk_lanes(const Exec &E, uint32_t q)
-{
-    const uint32_t part = (q + E.lane_div - 1) / E.lane_div;
-    return q < 8u || part > (uint32_t)WAVE ? (uint32_t)WAVE : (part < 8u ? 8u : part);
-}
-
-// Walks each wavefront of a launch takes by its own index, of q for each; 0:
-// all of them are given out so, evenly.
-__device__ __forceinline__ uint32_t first_share(const Exec &E, uint32_t q, uint32_t lanes)
-{
-    if (lanes >= q) return 0;
-    return E.lane_div > 1 ? lanes : (q < (uint32_t)POOL ? q : (uint32_t)POOL);
-}
-
 // Six wavefronts per SIMD (80 registers) hide more of the hub moves' latency
 // than five: scale 22 skewed 370 -> 353 ms, FN-Approx on Skew-5 97.6 -> 88.5
 // ms, visit counts at scale 21 132 -> 119 ms, scale 18 without sketches 26.7 ->
@@ -1681,8 +1659,8 @@ __global__ __launch_bounds__(PBLOCK, K == PLAIN_ENTRIES ? 6 : 5) void k_persiste
     // that no wavefront holds unstarted walks while others have run dry.
     const uint32_t nwaves = gridDim.x * (PBLOCK / WAVE);
     const uint32_t wid = blockIdx.x * (PBLOCK / WAVE) + wv;
-    const uint32_t lanes = walk_lanes(E, total / nwaves);
-    const uint32_t share0 = first_share(E, total / nwaves, lanes);
+    const uint32_t lanes = walk_lanes(E.lane_div, split_share(total, nwaves));
+    const uint32_t share0 = first_share(E.lane_div, total, nwaves, lanes);
     const uint32_t given = share0 ? nwaves * share0 : total;  // walks given out by index
     uint32_t pool_next = share0 ? wid * share0 : (uint32_t)((uint64_t)total * wid / nwaves);
     uint32_t pool_end = share0 ? pool_next + share0 : (uint32_t)((uint64_t)total * (wid + 1) / nwaves);
@@ -2165,18 +2143,7 @@ uint32_t persistent_blocks(const n2v_exec_opts &o, int dev, Kind K, uint32_t wg_
     if (!o.waves_per_cu && per_cu > wg_cap) per_cu = wg_cap;
     if (per_cu > (uint32_t)d.occ[K]) per_cu = d.occ[K];
     if (per_cu < 1) per_cu = 1;
-    uint64_t blocks = (uint64_t)d.cus * per_cu;
-    // Small jobs: down to a wavefront per walk.  Past a walk per wavefront, a
-    // job with hardly any hub moves fills its lanes first (but for two wavefronts per
-    // SIMD, which hide each other's latency): rounds with part of the lanes
-    // cost as many instructions (112,086 walks, weighted, degree 100: 0.90
-    // against 1.00 ms).
-    uint64_t waves = walks;
-    if (few_hubs && walks > blocks * (PBLOCK / WAVE)) waves = std::max<uint64_t>(walks / WAVE, 8ull * d.cus);
-    const uint64_t need = (waves + PBLOCK / WAVE - 1) / (PBLOCK / WAVE);
-    if (blocks > need) blocks = need;
-    if (blocks < 1) blocks = 1;
-    return (uint32_t)blocks;
+    return split_blocks(walks, (uint64_t)d.cus * per_cu, (uint32_t)d.cus, few_hubs);
 }
 
 template <bool W, bool C>
