@@ -29,6 +29,7 @@
 #include <mutex>
 #include <new>
 
+#include "perdev.hpp"
 #include "prims.hpp"
 #include "split.hpp"
 #include "walk.hpp"
@@ -2107,11 +2108,10 @@ struct DevInfo {
     int occ[3] = {};  // workgroups of the persistent kernel per CU, by Kind
 };
 
-DevInfo &dev_info(int dev)
+const DevInfo &dev_info(int dev)
 {
-    static DevInfo info[64];
-    DevInfo &d = info[dev & 63];
-    if (d.cus == 0) {
+    static PerDevice<DevInfo> info;
+    return info.get(dev, [dev](DevInfo &d) {
         hipDeviceProp_t prop;
         if (hipGetDeviceProperties(&prop, dev) == hipSuccess) d.cus = prop.multiProcessorCount;
         if (d.cus <= 0) d.cus = 256;
@@ -2123,8 +2123,7 @@ DevInfo &dev_info(int dev)
             (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, kernels[k], PBLOCK, 0);
             d.occ[k] = b > 0 ? b : 2;
         }
-    }
-    return d;
+    });
 }
 
 size_t plain_ws(uint32_t n_starts, uint32_t L)
@@ -2138,7 +2137,7 @@ size_t plain_ws(uint32_t n_starts, uint32_t L)
 
 uint32_t persistent_blocks(const n2v_exec_opts &o, int dev, Kind K, uint32_t wg_cap, uint64_t walks, bool few_hubs)
 {
-    DevInfo &d = dev_info(dev);
+    const DevInfo &d = dev_info(dev);
     uint32_t per_cu = o.waves_per_cu ? (o.waves_per_cu + (PBLOCK / WAVE) - 1) / (PBLOCK / WAVE) : (uint32_t)d.occ[K];
     if (!o.waves_per_cu && per_cu > wg_cap) per_cu = wg_cap;
     if (per_cu > (uint32_t)d.occ[K]) per_cu = d.occ[K];
@@ -2187,7 +2186,7 @@ int launch_plain_kind(const Exec &E, const OneJob &S, void *ws, int dev, hipStre
     hipLaunchKernelGGL(k_zero, dim3(1), dim3(256), 0, st, hubn, 4 * (S.c.L + 1));
     hipLaunchKernelGGL((k_plain_init<W, C>), dim3(blocks), dim3(256), 0, st, E, S, state);
     N2V_HIP(hipGetLastError());
-    DevInfo &d = dev_info(dev);
+    const DevInfo &d = dev_info(dev);
     const uint32_t hub_blocks = (uint32_t)d.cus * 8;
     // A superstep lasts as long as its slowest chain of dependent reads: while
     // the walks fill no more than the chip's 32 wavefronts per CU with 64 (8, 4)
@@ -2490,7 +2489,7 @@ int launch_plain_replayed(const n2v_graph *g, const Exec &E, const OneJob &S, vo
 
 uint32_t full_grid_blocks(const Exec &E, int dev)
 {
-    DevInfo &d = dev_info(dev);
+    const DevInfo &d = dev_info(dev);
     return (uint32_t)d.cus * std::min((uint32_t)d.occ[kind_of(E)], E.wg_cap);
 }
 
