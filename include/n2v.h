@@ -152,7 +152,10 @@ enum { N2V_OUT_WALKS = 1, N2V_OUT_COUNTS = 2 };
 
 typedef struct {
     int mode;            /* N2V_MODE_*; AUTO = PERSISTENT */
-    uint32_t t_wave;     /* persistent: rejection moves at degree > t_wave run wave-cooperatively */
+    uint32_t t_wave;     /* persistent: rejection moves at degree > t_wave run wave-cooperatively.  The
+                            default, 1024, also lets a walk call with no more walks than wavefronts, on
+                            a graph with less than a tenth of its entries in hub rows, make all its
+                            moves so; every other value is taken as it is */
     uint32_t t_sparse;   /* hub moves use the sparse intersection when deg(t) <= t_sparse (default
                             1023; the sparse path holds 895) ... */
     uint32_t sparse_ratio; /* ... and deg(t) * sparse_ratio * log2(deg v) < deg(v) + deg(t) */

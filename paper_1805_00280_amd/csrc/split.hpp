@@ -63,4 +63,21 @@ constexpr uint32_t first_share(uint32_t lane_div, uint32_t total, uint32_t nwave
     return lane_div > 1 ? lanes : (q < POOL ? q : POOL);
 }
 
+// A walk alone on its wavefront lasts as long as its chain of attempts: under
+// the default option the wavefront makes 64 of a move at once (t_wave 0; 1000
+// walks of 40 moves on ER-20: 139 -> 75 us).  Not where hubs are common, whose
+// lines the other 60 attempts' reads push out (100 walks at scale 16: 165
+// against 194 us).  Any other t_wave is the caller's, and stays.
+constexpr uint32_t T_WAVE_DEFAULT = 1024;
+
+constexpr bool lone_walks(uint32_t walks, uint32_t blocks, uint32_t lane_div)
+{
+    return lane_div == 1 && walks <= blocks * SPLIT_WAVES;
+}
+
+constexpr uint32_t launch_t_wave(uint32_t t_wave, bool lone)
+{
+    return lone && t_wave == T_WAVE_DEFAULT ? 0u : t_wave;
+}
+
 }  // namespace n2v

@@ -124,7 +124,12 @@ extern "C" int n2v_autotune(n2v_graph *g, uint32_t n_walks, uint32_t L, float p,
     const uint32_t ratio_c[] = {1, 2, 4, 8, 16, 32, 1u << 20};
     const uint32_t waves_c[] = {0, 8, 12, 16};
     const uint32_t search_c[] = {0, 2, 4, 8, 16, 64, 0xFFFFFFFFu};
-    for (int pass = 0; pass < 4; ++pass) {
+    // a sample whose walks each have a wavefront says nothing about t_wave in
+    // larger launches: the default stays, which serves both
+    Exec E0;
+    make_exec(g, cur, &E0);
+    const bool lone = lone_launch(E0, cur, g->device, n_walks);
+    for (int pass = lone ? 1 : 0; pass < 4; ++pass) {
         const uint32_t *vals = pass == 0 ? t_wave_c : pass == 1 ? ratio_c : pass == 2 ? waves_c : search_c;
         const int nv = pass == 0 ? 7 : pass == 1 ? 7 : pass == 2 ? 4 : 7;
         for (int i = 0; i < nv; ++i) {

@@ -2157,11 +2157,7 @@ int launch_persistent(const Exec &E_opts, const OneJob &S_opts, const n2v_exec_o
     S.c.hist = C && E.g.n <= HIST_MAX && (uint64_t)S.n * S.c.L >= 64ull * E.g.n;
     if (S.c.hist) blocks = std::min(blocks, 3u * (uint32_t)dev_info(dev).cus);
     const size_t lds = S.c.hist ? E.g.n * sizeof(uint32_t) : 0;
-    // A walk alone on its wavefront lasts as long as its chain of attempts:
-    // the wavefront makes 64 of a move at once (1000 walks of 40 moves on
-    // ER-20: 139 -> 75 us).  Not where hubs are common, whose lines the other
-    // 60 attempts' reads push out (100 walks at scale 16: 165 against 194 us).
-    if (E.lane_div == 1 && S.n <= blocks * (PBLOCK / WAVE)) E.t_wave = 0;
+    E.t_wave = launch_t_wave(E.t_wave, lone_walks(S.n, blocks, E.lane_div));
     hipLaunchKernelGGL(k_zero, dim3(1), dim3(64), 0, st, S.cur, 1u);
     auto kernel = K == WEIGHTED       ? k_persistent<OneJob, W, C, WEIGHTED>
                   : K == WIDE_ENTRIES ? k_persistent<OneJob, W, C, WIDE_ENTRIES>
@@ -2487,6 +2483,11 @@ int launch_plain_replayed(const n2v_graph *g, const Exec &E, const OneJob &S, vo
     return N2V_OK;
 }
 
+bool lone_launch(const Exec &E, const n2v_exec_opts &o, int dev, uint32_t walks)
+{
+    return lone_walks(walks, persistent_blocks(o, dev, kind_of(E), E.wg_cap, walks, E.thread_iters > 4), E.lane_div);
+}
+
 uint32_t full_grid_blocks(const Exec &E, int dev)
 {
     const DevInfo &d = dev_info(dev);
@@ -2531,7 +2532,7 @@ extern "C" void n2v_exec_opts_default(const n2v_graph *g, n2v_exec_opts *o)
         return;
     }
     o->mode = N2V_MODE_AUTO;
-    o->t_wave = 1024;
+    o->t_wave = T_WAVE_DEFAULT;
     o->t_sparse = 1023;
     o->sparse_ratio = 2;
     o->waves_per_cu = 0;

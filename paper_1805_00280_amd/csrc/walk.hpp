@@ -56,6 +56,9 @@ struct alignas(256) TableHdr {
 int walk_multipliers(float p, float q, uint32_t *A_ret, uint32_t *A_out);
 void make_exec(const n2v_graph *g, const n2v_exec_opts &o, Exec *E);
 uint32_t full_grid_blocks(const Exec &E, int dev);
+// Whether a persistent launch of `walks` walks gives each a wavefront that makes
+// its attempts together under the default t_wave.
+bool lone_launch(const Exec &E, const n2v_exec_opts &o, int dev, uint32_t walks);
 int launch_job_table(const Exec &E, const TableHdr *hdr, uint32_t blocks, hipStream_t st);
 // One persistent launch of a single job on the graph's walk counters.
 int launch_one(const n2v_graph *g, const Exec &E, const JobCtx &c, const uint32_t *starts, uint32_t n,

@@ -47,12 +47,40 @@ int main()
 }
 """
 
+T_WAVE = r"""
+#include <stdio.h>
+#include "split.hpp"
+using namespace n2v;
+int main()
+{
+    const uint32_t t_waves[] = {0, 1, 8, 512, 1023, 1024, 1025, 4096, 0xFFFFFFFFu};
+    const uint32_t walk_counts[] = {1, 1000, 5120, 5121, 100000};
+    for (uint32_t lane_div = 1; lane_div <= 8; ++lane_div)
+        for (uint32_t walks : walk_counts)
+            for (uint32_t t : t_waves) {
+                const uint32_t blocks = split_blocks(walks, 1280, 256, lane_div == 1);
+                const uint32_t got = launch_t_wave(t, lone_walks(walks, blocks, lane_div));
+                const uint32_t want = t == 1024 && lane_div == 1 && walks <= 5120 ? 0 : t;
+                if (got != want) printf("t_wave %u, %u walks, lane_div %u: %u\n", t, walks, lane_div, got);
+            }
+    return 0;
+}
+"""
 
-def test_a_wavefront_has_a_lane_for_every_walk_it_is_given(tmp_path):
+
+def run(tmp_path, text):
     if shutil.which("g++") is None:
         pytest.skip("g++ not available")
     src, exe = tmp_path / "split.cpp", tmp_path / "split"
-    src.write_text(DRIVER)
+    src.write_text(text)
     subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I", CSRC, str(src), "-o", str(exe)])
     out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
     assert out.returncode == 0 and out.stdout == "", out.stdout[:2000]
+
+
+def test_a_wavefront_has_a_lane_for_every_walk_it_is_given(tmp_path):
+    run(tmp_path, DRIVER)
+
+
+def test_only_the_default_t_wave_changes_for_lone_walks(tmp_path):
+    run(tmp_path, T_WAVE)
