@@ -80,4 +80,45 @@ constexpr uint32_t launch_t_wave(uint32_t t_wave, bool lone)
     return lone && t_wave == T_WAVE_DEFAULT ? 0u : t_wave;
 }
 
+// Whether a plain superstep may make its hub moves itself, each with one
+// wavefront: where they are rare (lane_div 1), and either the caller left t_wg
+// at its default or no row can be longer than it (a longer one alone would have
+// more entries than all hub rows).  At the default even long rows are better
+// off so: walks of 40 moves from one of two adjacent hubs of 300,000, 100 / 5000
+// / 60,000 of them, 0.33 / 0.49 / 3.13 ms against 0.59 / 0.85 / 3.50 ms queued.
+// A t_wg of the caller's own asks for workgroups, which take queued moves.
+constexpr uint32_t T_WG_DEFAULT = 65536;
+
+constexpr bool plain_may_fuse(uint32_t lane_div, uint32_t t_wg, uint64_t hub_entries)
+{
+    return lane_div == 1 && (t_wg == T_WG_DEFAULT || hub_entries <= t_wg);
+}
+
+// Lanes that make a walk's attempts in a superstep of the plain form, and
+// whether the superstep makes its hub moves in the same launch.
+struct PlainSplit {
+    int lanes;
+    bool fused;
+};
+
+// A superstep lasts as long as its slowest chain of dependent reads: while
+// the walks fill no more than the chip's 32 wavefronts per CU with 64 (8, 4)
+// lanes each, as many take a walk's attempts.  Where hub moves are rare
+// those wavefronts make them too, and the superstep is one launch (40,960
+// walks of 80 moves at scale 12: 2.33 -> 1.35 ms; 10,000 of 40 on ER-18 0.70
+// -> 0.28 ms).  Where they are common they are queued, each wavefront's with
+// one atomic on the queue's counter, so groups pay off only for fewer
+// walks: 1 / 4 / 8 / 64 lanes measured 2.98 / 2.62 / 2.84 / 3.40 ms for
+// 20,000 walks at scale 16, 9.1 / 10.2 / 11.6 / 14.5 ms for 100,000, 2.47 /
+// 1.87 / 1.77 / 1.84 ms for 3000.  Counting adds each workgroup's checksum at one
+// address: no more of them than a quarter of the walks' wavefronts need.
+constexpr PlainSplit plain_split(uint32_t walks, uint32_t cus, bool fuse, bool counts)
+{
+    const uint32_t slots = cus * 32u * SPLIT_LANES;
+    int lanes = fuse ? (walks <= slots / 64 ? 64 : (walks <= slots / 8 ? 8 : (walks <= slots / 2 ? 4 : 1)))
+                     : (walks <= slots / 64 ? 8 : (walks <= slots / 16 ? 4 : 1));
+    if (counts && lanes > 4) lanes = walks <= slots / 512 ? 8 : 4;
+    return PlainSplit{lanes, fuse && lanes >= 4};
+}
+
 }  // namespace n2v

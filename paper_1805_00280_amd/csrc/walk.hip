@@ -2184,24 +2184,9 @@ int launch_plain_kind(const Exec &E, const OneJob &S, void *ws, int dev, hipStre
     N2V_HIP(hipGetLastError());
     const DevInfo &d = dev_info(dev);
     const uint32_t hub_blocks = (uint32_t)d.cus * 8;
-    // A superstep lasts as long as its slowest chain of dependent reads: while
-    // the walks fill no more than the chip's 32 wavefronts per CU with 64 (8, 4)
-    // lanes each, as many take a walk's attempts.  Where hub moves are rare
-    // those wavefronts make them too, and the superstep is one launch (40,960
-    // walks of 80 moves at scale 12: 2.33 -> 1.35 ms; 10,000 of 40 on ER-18 0.70
-    // -> 0.28 ms).  Where they are common they are queued, each wavefront's with
-    // one atomic on the queue's counter, so groups pay off only for fewer
-    // walks: 1 / 4 / 8 / 64 lanes measured 2.98 / 2.62 / 2.84 / 3.40 ms for
-    // 20,000 walks at scale 16, 9.1 / 10.2 / 11.6 / 14.5 ms for 100,000, 2.47 /
-    // 1.87 / 1.77 / 1.84 ms for 3000.
-    const uint32_t slots = (uint32_t)d.cus * 32u * WAVE;
-    const bool few_hubs = E.lane_div == 1;
-    int grp = few_hubs ? (S.n <= slots / 64 ? 64 : (S.n <= slots / 8 ? 8 : (S.n <= slots / 2 ? 4 : 1)))
-                       : (S.n <= slots / 64 ? 8 : (S.n <= slots / 16 ? 4 : 1));
-    // counting adds each workgroup's checksum at one address: no more of them
-    // than a quarter of the walks' wavefronts need
-    if (C && grp > 4) grp = S.n <= slots / 512 ? 8 : 4;
-    const bool fused = grp >= 4 && few_hubs;
+    const PlainSplit ps = plain_split(S.n, (uint32_t)d.cus, E.plain_fuse != 0, C);
+    const int grp = ps.lanes;
+    const bool fused = ps.fused;
     auto step = grp == 64  ? k_plain_step<W, C, K, 64, true>
                 : grp == 8 ? (fused ? k_plain_step<W, C, K, 8, true> : k_plain_step<W, C, K, 8, false>)
                 : grp == 4 ? (fused ? k_plain_step<W, C, K, 4, true> : k_plain_step<W, C, K, 4, false>)
@@ -2353,6 +2338,7 @@ void make_exec(const n2v_graph *g, const n2v_exec_opts &o, Exec *E)
     // 1 up to 10% of the entries in hub rows, 8 from 40% (see walk_lanes)
     const uint64_t twentieths = m ? he * 20 / m : 0;
     E->lane_div = twentieths < 1 ? 1u : (twentieths > 8 ? 8u : (uint32_t)twentieths);
+    E->plain_fuse = plain_may_fuse(E->lane_div, o.t_wg, he);
     // Workgroups per CU: all that fit, but five where the hub rows alone exceed
     // twice the 256 MB last-level cache: more merges at once then read more of
     // their lines from memory (scale 24 skewed: L2 hit rate 28%, 290 G line
@@ -2369,7 +2355,7 @@ PlainKey plain_key(const Exec &E, const OneJob &S, const void *ws, uint32_t hub_
 {
     // every field the launches read from the host: a new field of Exec,
     // DevGraph, JobCtx or OneJob must be added here
-    static_assert(sizeof(DevGraph) == 128 && sizeof(Exec) == 168 && sizeof(JobCtx) == 56 && sizeof(OneJob) == 80,
+    static_assert(sizeof(DevGraph) == 128 && sizeof(Exec) == 176 && sizeof(JobCtx) == 56 && sizeof(OneJob) == 80,
                   "plain_key covers every launch argument");
     PlainKey k;
     const DevGraph &d = E.g;
@@ -2392,7 +2378,7 @@ PlainKey plain_key(const Exec &E, const OneJob &S, const void *ws, uint32_t hub_
     k.put2(E.sparse_ratio, E.t_wg);
     k.put2(E.search_ratio, hub_blocks);
     k.put2(E.thread_iters, E.lane_div);
-    k.put(E.wg_cap);
+    k.put2(E.wg_cap, E.plain_fuse);
     k.put(E.cursor);
     k.put(S.c.out);
     k.put(S.c.cnt);
@@ -2538,7 +2524,7 @@ extern "C" void n2v_exec_opts_default(const n2v_graph *g, n2v_exec_opts *o)
     o->waves_per_cu = 0;
     o->block = 256;
     o->memo = 1;
-    o->t_wg = 65536;
+    o->t_wg = T_WG_DEFAULT;
     o->search_ratio = 24;
 }
 

@@ -18,6 +18,7 @@ struct Exec {
     uint32_t thread_iters;  // persistent form: attempts per lane before the wave serves pending walks
     uint32_t lane_div;      // persistent form: a wavefront starts one in lane_div of its walks at once
     uint32_t wg_cap;        // persistent form: most workgroups per CU
+    uint32_t plain_fuse;    // plain form: a superstep may make its hub moves itself
     uint32_t *cursor;       // walk counter of a single-job launch (taken per launch, zeroed before it)
 };
 

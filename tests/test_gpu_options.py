@@ -3,6 +3,7 @@ the autotuner keeps what a small sample cannot tell."""
 import numpy as np
 import pytest
 
+import oracle as O
 import paper_1805_00280_amd as P
 from gpuhelp import first_mismatch, gpu_graph_from_oracle, gpu_walk, oracle_rmat, oracle_walk, torch_cuda
 
@@ -34,3 +35,22 @@ def test_autotune_of_lone_walks_keeps_the_default_t_wave():
         g = gpu_graph_from_oracle(og)
         g.autotune(n, 20, 0.5, 2.0)
         assert P.exec_opts(g).t_wave == 1024, n
+
+
+@pytest.mark.parametrize("t_wg", [0, 1100, 65535, 65536])
+def test_t_wg_where_hub_rows_are_few(t_wg):
+    # two adjacent hubs with common neighbours hold 7% of the entries; every hub
+    # move takes the dense merge, in the step's launch or by a workgroup
+    torch_cuda()
+    rng = np.random.default_rng(2)
+    n = 3000
+    e = rng.integers(2, n, (40_000, 2))
+    hubs = [(h, int(v)) for h in (0, 1) for v in rng.choice(n - 2, 1500, replace=False) + 2] + [(0, 1)]
+    og = O.CSR.from_edges(n, [(int(a), int(b)) for a, b in e if a != b] + hubs)
+    g = gpu_graph_from_oracle(og)
+    for count in (3, 500, 9000):
+        starts = np.zeros(count, dtype=np.uint32)
+        starts[1::2] = np.arange(count // 2, dtype=np.uint32) % n
+        want = oracle_walk(og, starts, 12, 0.25, 4.0, 21)
+        got = gpu_walk(g, starts, 12, 0.25, 4.0, 21, mode=P.MODE_PLAIN, t_wg=t_wg, sparse_ratio=1 << 20)
+        assert first_mismatch(got, want) is None, (count, first_mismatch(got, want))

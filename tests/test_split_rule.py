@@ -67,6 +67,33 @@ int main()
 }
 """
 
+PLAIN = r"""
+#include <stdio.h>
+#include "split.hpp"
+using namespace n2v;
+int main()
+{
+    const uint32_t t_wgs[] = {0, 100, 65535, 65536, 65537, 0xFFFFFFFFu};
+    const uint64_t hubs[] = {0, 1, 100, 101, 65536, 65537, 1ull << 33};
+    for (uint32_t lane_div = 1; lane_div <= 8; ++lane_div)
+        for (uint32_t t : t_wgs)
+            for (uint64_t he : hubs) {
+                const bool may = plain_may_fuse(lane_div, t, he);
+                // a caller's own t_wg that some row may exceed keeps its workgroups
+                if (may && (lane_div > 1 || (t != 65536 && he > t))) printf("t_wg %u, %llu\n", t, (unsigned long long)he);
+                if (!may && lane_div == 1 && he <= t) printf("t_wg %u, %llu not\n", t, (unsigned long long)he);
+                for (uint32_t walks = 1; walks && walks < 0x80000000u; walks = walks * 2 + walks % 3)
+                    for (int counts = 0; counts < 2; ++counts) {
+                        const PlainSplit p = plain_split(walks, 256, may, counts);
+                        // the instances that exist
+                        const bool ok = p.lanes == 1 ? !p.fused : p.lanes == 64 ? p.fused : p.lanes == 4 || p.lanes == 8;
+                        if (!ok || (p.fused && !may)) printf("%u walks: %d lanes, fused %d\n", walks, p.lanes, p.fused);
+                    }
+            }
+    return 0;
+}
+"""
+
 
 def run(tmp_path, text):
     if shutil.which("g++") is None:
@@ -84,3 +111,7 @@ def test_a_wavefront_has_a_lane_for_every_walk_it_is_given(tmp_path):
 
 def test_only_the_default_t_wave_changes_for_lone_walks(tmp_path):
     run(tmp_path, T_WAVE)
+
+
+def test_plain_supersteps_queue_the_moves_a_callers_t_wg_asks_for(tmp_path):
+    run(tmp_path, PLAIN)
