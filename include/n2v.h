@@ -122,7 +122,14 @@ typedef struct {
 /* Fills the defaults above. */
 void n2v_graph_opts_default(n2v_graph_opts *o);
 
-/* Workspace bytes for a graph with n vertices and m entries. */
+/* Workspace bytes for a graph with n vertices and m entries: 8 per entry and
+ * about 24 (weighted 32) per vertex that every graph needs, and two parts that
+ * only speed walks up and are left out where the workspace given to
+ * n2v_graph_create does not hold them: 2 bytes per entry for membership
+ * filters (m <= 2^33) and 8 more per entry of an unweighted graph with n >=
+ * 2^18, m <= 32 n and m <= 2^31, used where rows of degree > d_rule hold less
+ * than 2% of the entries.  A workspace sized for a weighted graph holds an
+ * unweighted one of the same n and m, without the last part. */
 int n2v_graph_workspace(uint32_t n, uint64_t m, int weighted, size_t *ws_bytes);
 
 /* Contract: off[0] = 0, off[n] = m, off non-decreasing; each row strictly

@@ -194,9 +194,7 @@ class Graph:
         self.n = int(n if n is not None else off.numel() - 1)
         self.m = int(adj.numel())
         self.device = off.device
-        ws = C.c_size_t()
-        check(lib().n2v_graph_workspace(self.n, self.m, int(wt is not None), C.byref(ws)), "n2v_graph_workspace")
-        self.ws = _alloc(ws.value, self.device)
+        self.ws = _alloc(self._workspace_bytes(d_rule, stream), self.device)
         o = GraphOpts(d_rule, a_cap, validate)
         h = C.c_void_p()
         check(lib().n2v_graph_create(_ptr(off), _ptr(adj), _ptr(wt), self.n, self.m, C.byref(o), _ptr(self.ws),
@@ -207,6 +205,22 @@ class Graph:
         self.memo = None
         self.memo_min_degree = None
         del torch
+
+    def _workspace_bytes(self, d_rule, stream):
+        """Bytes the graph's workspace needs.  The query for an unweighted graph may hold 8 bytes per entry that
+        are used only where rows of degree > d_rule have less than 2% of the entries.  Where that is 256 MB or
+        more and they have more, the weighted graph's size, which is without, does (three small kernels and a
+        wait against a creation of tens of milliseconds)."""
+        ws, wsw = C.c_size_t(), C.c_size_t()
+        check(lib().n2v_graph_workspace(self.n, self.m, int(self.wt is not None), C.byref(ws)), "n2v_graph_workspace")
+        if self.wt is None and self.m >= 1 << 25 and stream is None:
+            check(lib().n2v_graph_workspace(self.n, self.m, 1, C.byref(wsw)), "n2v_graph_workspace")
+            if wsw.value < ws.value:
+                off = self.off.view(_torch().int64)
+                deg = off[1:self.n + 1] - off[:self.n]
+                if 50 * int((deg * (deg > d_rule)).sum()) >= self.m:
+                    return wsw.value
+        return ws.value
 
     @staticmethod
     def generate_rmat(scale, edge_factor, a, b, c, seed, weighted=False, device="cuda", stream=None):

@@ -361,9 +361,9 @@ __global__ void k_zero_u32(uint32_t *p, uint32_t n)
 
 struct GraphLayout {
     VRec *vrec;
-    void *rec;  // entry records: uint4 where `wide`, and hub rows turn out few, else uint2
+    void *rec;       // entry records: uint4 where `wide`, and hub rows turn out few, else uint2
     bool wide;
-    uint64_t *filt;
+    uint64_t *filt;  // or null
     uint64_t *wsum;
     uint64_t *hbase;
     void *scan;
@@ -372,15 +372,18 @@ struct GraphLayout {
     uint32_t *cursors;
 };
 
-size_t graph_layout(uint32_t n, uint64_t m, int weighted, void *ws, size_t ws_bytes, GraphLayout *L)
+// Parts of the workspace that only speed walks up.
+enum Parts { NEEDED = 0, FILTER = 1, FILTER_WIDE = 2 };
+
+size_t graph_layout(uint32_t n, uint64_t m, int weighted, Parts parts, void *ws, size_t ws_bytes, GraphLayout *L)
 {
     Carver c(ws, ws_bytes);
     L->status = c.take<uint32_t>(64);
     L->cursors = c.take<uint32_t>((uint64_t)CURSOR_SLOTS * CURSOR_STRIDE);
     L->vrec = c.take<VRec>((uint64_t)n + 1);
-    L->wide = wide_entries(n, m, weighted);
+    L->wide = parts >= FILTER_WIDE && wide_entries(n, m, weighted);
     L->rec = L->wide ? (void *)c.take<uint4>(m ? m : 1) : (void *)c.take<uint2>(m ? m : 1);
-    L->filt = m <= FILTER_MAX_ENTRIES ? c.take<uint64_t>(filter_words(m)) : nullptr;
+    L->filt = parts >= FILTER && m <= FILTER_MAX_ENTRIES ? c.take<uint64_t>(filter_words(m)) : nullptr;
     L->wsum = weighted ? c.take<uint64_t>((uint64_t)n + 1) : nullptr;
     L->hbase = c.take<uint64_t>((uint64_t)n + 1);
     L->scan = c.take<char>(scan_scratch_bytes((uint64_t)n + 1));
@@ -429,7 +432,7 @@ extern "C" int n2v_graph_workspace(uint32_t n, uint64_t m, int weighted, size_t 
     if (!ws_bytes) return set_error(N2V_EINVAL, "n2v_graph_workspace: null ws_bytes");
     if (n == 0 || n > 0xFFFFFFFEu) return set_error(N2V_EINVAL, "n2v_graph_workspace: n out of range");
     GraphLayout L;
-    *ws_bytes = graph_layout(n, m, weighted, nullptr, 0, &L);
+    *ws_bytes = graph_layout(n, m, weighted, FILTER_WIDE, nullptr, 0, &L);
     return N2V_OK;
 }
 
@@ -447,7 +450,12 @@ extern "C" int n2v_graph_create(const uint64_t *off, const uint32_t *adj, const 
     if (opts) o = *opts;
     if (o.a_cap < 1) return set_error(N2V_EINVAL, "n2v_graph_create: a_cap must be >= 1");
     GraphLayout L;
-    size_t need = graph_layout(n, m, wt != nullptr, ws, ws_bytes, &L);
+    // a workspace without room for a part that only speeds walks up is still one
+    size_t need = 0;
+    for (const Parts parts : {FILTER_WIDE, FILTER, NEEDED}) {
+        need = graph_layout(n, m, wt != nullptr, parts, ws, ws_bytes, &L);
+        if (need <= ws_bytes) break;
+    }
     if (need > ws_bytes) return set_error(N2V_ENOMEM, "n2v_graph_create: workspace %zu < %zu bytes", ws_bytes, need);
     hipStream_t st = (hipStream_t)stream;
 
