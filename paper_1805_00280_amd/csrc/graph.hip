@@ -31,8 +31,21 @@ __global__ __launch_bounds__(256) void k_validate_off(const uint64_t *__restrict
 // whatever rows they belong to: with a wavefront per row, one hub row of 60 K
 // entries (each a dependent search) outlasted all the others together
 // (k_derive 17.7 ms at R-MAT scale 20, 112 ms at scale 22 skewed), and rows of
-// ten entries left 54 lanes idle.
+// ten entries left 54 lanes idle.  Small graphs take smaller chunks, down to a
+// wavefront's width, until CHUNK_WAVES wavefronts (one per SIMD) have one: the
+// rounds of a chunk wait for each other (creation at scale 9 158 -> 120 us, at
+// scale 14 191 -> 163 us; with four per SIMD 121 and 220 us, and 267 against
+// 210 us for 4096 vertices of degree 100, each chunk finding its rows first;
+// with its memory cleared by one launch and two copies back scale 9 takes 112).
 constexpr uint32_t CHUNK = 1024;
+constexpr uint64_t CHUNK_WAVES = 1024;
+
+__host__ __device__ inline uint32_t chunk_of(uint64_t m)
+{
+    uint32_t c = CHUNK;
+    while (c > (uint32_t)WAVE && m < c * CHUNK_WAVES) c >>= 1;
+    return c;
+}
 
 // Last row whose offset is at or below e (so that, offsets ascending, the row
 // that holds entry e): 64 probes a round.
@@ -51,12 +64,13 @@ __device__ uint64_t row_of(const uint64_t *__restrict__ off, uint64_t n, uint64_
 }
 
 // mark[i] = the row that begins at entry c0 + i, SENT where none does, for
-// the chunk [c0, c0 + cnt).  Returns the row that holds c0.
-__device__ uint32_t mark_rows(const uint64_t *__restrict__ off, uint32_t n, uint64_t c0, uint32_t cnt,
+// the chunk [c0, c0 + cnt) of at most `chunk` entries.  Returns the row that
+// holds c0.
+__device__ uint32_t mark_rows(const uint64_t *__restrict__ off, uint32_t n, uint64_t c0, uint32_t cnt, uint32_t chunk,
                               uint32_t *mark)
 {
     const int l = lane_id();
-    for (uint32_t i = l; i < CHUNK; i += WAVE) mark[i] = SENT;
+    for (uint32_t i = l; i < chunk; i += WAVE) mark[i] = SENT;
     wave_lds_sync();
     const uint64_t r0 = row_of(off, n, c0);
     const uint64_t end = c0 + cnt;
@@ -102,12 +116,13 @@ __device__ __forceinline__ void each_entry(const uint64_t *__restrict__ off, uin
     __shared__ uint32_t marks[256 / WAVE][CHUNK];
     uint32_t *mark = marks[threadIdx.x / WAVE];
     const int l = lane_id();
-    const uint64_t chunks = (m + CHUNK - 1) / CHUNK;
+    const uint32_t chunk = chunk_of(m);
+    const uint64_t chunks = (m + chunk - 1) / chunk;
     const uint64_t nw = (uint64_t)gridDim.x * (256 / WAVE);
     for (uint64_t c = (uint64_t)blockIdx.x * (256 / WAVE) + threadIdx.x / WAVE; c < chunks; c += nw) {
-        const uint64_t c0 = c * CHUNK;
-        const uint32_t cnt = m - c0 < CHUNK ? (uint32_t)(m - c0) : CHUNK;
-        uint32_t row = mark_rows(off, n, c0, cnt, mark);
+        const uint64_t c0 = c * chunk;
+        const uint32_t cnt = m - c0 < chunk ? (uint32_t)(m - c0) : chunk;
+        uint32_t row = mark_rows(off, n, c0, cnt, chunk, mark);
         for (uint32_t i0 = 0; i0 < cnt; i0 += WAVE) {
             const uint32_t mk = mark[i0 + l];
             const uint32_t v = row_scan(mk, row);
@@ -268,10 +283,16 @@ __global__ __launch_bounds__(256) void k_reverse(const uint64_t *__restrict__ of
     if (lane_id() == 0 && found) atomicAdd(paired, (unsigned long long)found);
 }
 
-__global__ void k_fill0_u64(uint64_t *p, uint64_t n)
+// Clears the graph's device flags, its first statistics words (paired entries,
+// entries in hub rows, weight range) and its filters (words: 0 without).
+__global__ __launch_bounds__(256) void k_clear(uint32_t *__restrict__ status, unsigned long long *__restrict__ hist,
+                                               uint64_t *__restrict__ filt, uint64_t words)
 {
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = 0;
+    const uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t < 64) status[t] = 0;
+    if (t < 3) hist[t] = 0;
+    for (uint64_t i = t; i < words; i += stride) filt[i] = 0;
 }
 
 // Sketch words of a vertex of degree d: d rows of memo_row_words(d).
@@ -401,7 +422,8 @@ uint32_t grid_for_threads(uint64_t count)
 // 256 CUs hold (each wavefront ends with one atomic on one address).
 uint32_t grid_for_entries(uint64_t m)
 {
-    const uint64_t blocks = (m + 4 * CHUNK - 1) / (4 * CHUNK);
+    const uint64_t per = 4 * chunk_of(m);
+    const uint64_t blocks = (m + per - 1) / per;
     return (uint32_t)(blocks > 4096 ? 4096 : (blocks < 1 ? 1 : blocks));
 }
 
@@ -459,7 +481,8 @@ extern "C" int n2v_graph_create(const uint64_t *off, const uint32_t *adj, const 
     if (need > ws_bytes) return set_error(N2V_ENOMEM, "n2v_graph_create: workspace %zu < %zu bytes", ws_bytes, need);
     hipStream_t st = (hipStream_t)stream;
 
-    hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, st, L.status, 64u);
+    const uint64_t fwords = L.filt ? filter_words(m) : 0;
+    hipLaunchKernelGGL(k_clear, dim3(grid_for_threads(fwords)), dim3(256), 0, st, L.status, L.hist, L.filt, fwords);
     N2V_HIP(hipGetLastError());
     if (o.validate >= 1) {
         hipLaunchKernelGGL(k_validate_off, dim3(grid_for_threads(n)), dim3(256), 0, st, off, n, m, L.status + 1);
@@ -476,20 +499,16 @@ extern "C" int n2v_graph_create(const uint64_t *off, const uint32_t *adj, const 
     }
     if (wt)
         hipLaunchKernelGGL(k_vrec_w, dim3(std::min(grid_for_waves(n), 4096u)), dim3(256), 0, st, off, wt, n, L.vrec, L.wsum,
-                           L.status + 2);
+                           (uint32_t *)(L.hist + 2));
     else
         hipLaunchKernelGGL(k_vrec, dim3(grid_for_threads(n)), dim3(256), 0, st, off, n, L.vrec);
-    if (L.filt)
-        hipLaunchKernelGGL(k_fill0_u64, dim3(grid_for_threads(filter_words(m))), dim3(256), 0, st, L.filt,
-                           filter_words(m));
     // entries in hub rows: they decide the kind of entry records here and the
     // walk kernels' attempts per phase later
     const uint64_t memo_min = (uint64_t)o.d_rule + 1;
-    unsigned long long hub_entries = 0;
-    hipLaunchKernelGGL(k_zero_u64w, dim3(1), dim3(64), 0, st, L.hist, 2u);
     hipLaunchKernelGGL(k_deg_entries_ge, dim3(grid_for_waves(n)), dim3(256), 0, st, off, n, memo_min, L.hist + 1);
     bool wide = L.wide;
     if (wide) {
+        unsigned long long hub_entries = 0;
         N2V_HIP(hipMemcpyAsync(&hub_entries, L.hist + 1, sizeof(hub_entries), hipMemcpyDeviceToHost, st));
         N2V_HIP(hipStreamSynchronize(st));
         wide = hub_entries * 50 < m;
@@ -512,10 +531,12 @@ extern "C" int n2v_graph_create(const uint64_t *off, const uint32_t *adj, const 
     int rc = exclusive_scan_u64(L.hbase, (uint64_t)n + 1, L.scan, st);
     if (rc) return rc;
     uint64_t hub_words = 0;
-    uint32_t wrange[2] = {0, 0};
-    N2V_HIP(hipMemcpyAsync(&hub_entries, L.hist + 1, sizeof(hub_entries), hipMemcpyDeviceToHost, st));
+    struct {
+        unsigned long long hub_entries;
+        uint32_t wrange[2];
+    } stats = {0, {0, 0}};
+    N2V_HIP(hipMemcpyAsync(&stats, L.hist + 1, sizeof(stats), hipMemcpyDeviceToHost, st));
     N2V_HIP(hipMemcpyAsync(&hub_words, L.hbase + n, sizeof(uint64_t), hipMemcpyDeviceToHost, st));
-    N2V_HIP(hipMemcpyAsync(wrange, L.status + 2, sizeof(wrange), hipMemcpyDeviceToHost, st));
     N2V_HIP(hipStreamSynchronize(st));
     n2v_graph *g = (n2v_graph *)calloc(1, sizeof(n2v_graph));
     if (!g) return set_error(N2V_ENOMEM, "n2v_graph_create: host allocation failed");
@@ -529,7 +550,7 @@ extern "C" int n2v_graph_create(const uint64_t *off, const uint32_t *adj, const 
     g->dg.hbase = L.hbase;
     g->dg.memo = nullptr;
     g->hub_words = hub_words;
-    g->hub_entries = hub_entries;
+    g->hub_entries = stats.hub_entries;
     g->memo_words = hub_words;
     g->scan = L.scan;
     g->memo_bytes = 0;
@@ -551,8 +572,8 @@ extern "C" int n2v_graph_create(const uint64_t *off, const uint32_t *adj, const 
     g->dg.wlo = 1;
     g->dg.whi = 1;
     if (wt && m > 0) {
-        g->dg.wlo = 0xFFFFu - wrange[0];
-        g->dg.whi = wrange[1];
+        g->dg.wlo = 0xFFFFu - stats.wrange[0];
+        g->dg.whi = stats.wrange[1];
     }
     g->off = off;
     g->weighted = wt != nullptr;
