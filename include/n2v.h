@@ -206,13 +206,13 @@ int n2v_walk_workspace(const n2v_graph *g, uint32_t n_starts, uint32_t L,
  * 2^32, c, x, 3)).  Counts accumulate: zero them before the first chunk.
  * `opts` may be NULL (defaults); `ws` may be NULL when the query says 0.
  * The plain form (N2V_MODE_PLAIN) is one superstep per move (Algorithm 1): two
- * kernels, or one where hub moves are rare and the walks few.  A plain call whose every argument (pointers, sizes, options,
- * seed) equals that of one of the graph's last 8 distinct plain calls is
- * recorded into a HIP graph on its second occurrence and replayed from then
- * on: one graph launch instead of up to 2L+2 kernel launches, same results, and the
- * buffers' contents may change between calls.  Recording allocates the
- * graph's host and device memory; calls enqueued on a stream that is being
- * captured launch their kernels directly. */
+ * kernels, or one where hub moves are rare and the walks few.  A plain call
+ * whose every argument (pointers, sizes, options, seed) equals that of one of
+ * the graph's last 8 distinct plain calls is recorded into a HIP graph on its
+ * second occurrence and replayed from then on: one graph launch instead of up
+ * to 2L+2 kernel launches, same results, and the buffers' contents may change
+ * between calls.  Recording allocates the graph's host and device memory; calls
+ * enqueued on a stream that is being captured launch their kernels directly. */
 int n2v_walk_ex(const n2v_graph *g, const uint32_t *starts, uint32_t n_starts, uint64_t walk_base,
                 uint32_t L, float p, float q, uint64_t seed, const n2v_exec_opts *opts,
                 int outputs, uint32_t *out, uint32_t *cnt, uint64_t *checksum, void *ws,

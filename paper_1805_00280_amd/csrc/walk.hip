@@ -17,10 +17,11 @@
 //              chunked merge-intersection staged in LDS (dense) or by
 //              searching the members of a short N(t) in N(v) (sparse).
 //
-// Forms: PLAIN = one superstep per move (a thread kernel plus a hub kernel
-// with one workgroup per hub move, as a BSP superstep advances every walk by
-// one move); PERSISTENT = one launch, each wavefront owns 64 walk slots and
-// switches between thread and wave classes.
+// Forms: PLAIN = one superstep per move, as a BSP superstep advances every
+// walk by one move: a step kernel with 1 to 64 lanes per walk, which makes the
+// rare hub moves itself or queues them for a hub kernel (a workgroup or a
+// wavefront each); PERSISTENT = one launch, each wavefront owns 64 walk slots
+// and switches between thread and wave classes.
 #include <math.h>
 #include <stdlib.h>
 #include <string.h>
@@ -2234,11 +2235,11 @@ int walk_multipliers(float p, float q, uint32_t *A_ret, uint32_t *A_out)
 // so overlapping calls never share a counter.
 //
 // The same host record keeps the graph's captured plain-form launch
-// sequences.  The plain form issues 2L+2 kernels per call.  A call whose
+// sequences.  The plain form issues L+2 or 2L+2 kernels per call.  A call whose
 // every launch argument (graph view, options, job, starts, outputs,
 // workspace, grid) equals that of one of the last PLAIN_GRAPHS distinct calls
 // is recorded into a hipGraph on its second occurrence and replayed from then
-// on: one graph launch instead of 2L+2 kernel launches.  A replay runs exactly
+// on: one graph launch instead of all of them.  A replay runs exactly
 // the kernels, grids and arguments of the direct launches, so results are the
 // same; the contents of the buffers may change between calls.
 constexpr int PLAIN_GRAPHS = 8;
