@@ -2188,7 +2188,8 @@ int launch_plain_kind(const Exec &E, const OneJob &S, void *ws, int dev, hipStre
     const PlainSplit ps = plain_split(S.n, (uint32_t)d.cus, E.plain_fuse != 0, C);
     const int grp = ps.lanes;
     const bool fused = ps.fused;
-    auto step = grp == 64  ? k_plain_step<W, C, K, 64, true>
+    constexpr int MOST = C ? 8 : 64;  // plain_split's most lanes
+    auto step = grp > 8    ? k_plain_step<W, C, K, MOST, true>
                 : grp == 8 ? (fused ? k_plain_step<W, C, K, 8, true> : k_plain_step<W, C, K, 8, false>)
                 : grp == 4 ? (fused ? k_plain_step<W, C, K, 4, true> : k_plain_step<W, C, K, 4, false>)
                            : k_plain_step<W, C, K, 1, false>;

@@ -86,7 +86,7 @@ int main()
                     for (int counts = 0; counts < 2; ++counts) {
                         const PlainSplit p = plain_split(walks, 256, may, counts);
                         // the instances that exist
-                        const bool ok = p.lanes == 1 ? !p.fused : p.lanes == 64 ? p.fused : p.lanes == 4 || p.lanes == 8;
+                        const bool ok = p.lanes == 1 ? !p.fused : p.lanes == 64 ? p.fused && !counts : p.lanes == 4 || p.lanes == 8;
                         if (!ok || (p.fused && !may)) printf("%u walks: %d lanes, fused %d\n", walks, p.lanes, p.fused);
                     }
             }
