@@ -1,6 +1,7 @@
 """How a persistent launch splits its walks: by wavefront index, to part of the
-lanes, and from the shared counter, at the sizes where the rule changes (5120
-wavefronts hold the grid of a 256-CU device), on graphs without hub rows, with
+lanes, and from the shared counter, around the sizes where the rule changes (on
+a 256-CU device a weighted graph's grid has 5120 wavefronts, an unweighted
+one's 6144), on graphs without hub rows, with
 some, and with most entries in them; and the membership filter on rows whose
 words several rows share."""
 import numpy as np
