@@ -18,6 +18,9 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.environ.get("N2V_LIBRARY") or os.path.join(_HERE, "libn2v.so")
 SENT = 0xFFFFFFFF
 
+# Graphs of at least this many entries (8 GB at 8 bytes each) are given no workspace that they would not use.
+TRIM_ENTRIES = 1 << 30
+
 N2V_OK, N2V_PENDING = 0, 1
 ERRORS = {-1: "EINVAL", -2: "ENOMEM", -3: "EGRAPH", -4: "EDEVICE", -5: "EAGAIN", -6: "ETOOBIG", -7: "ENOTFOUND"}
 MODE_AUTO, MODE_PLAIN, MODE_PERSISTENT = 0, 1, 2
@@ -208,12 +211,12 @@ class Graph:
 
     def _workspace_bytes(self, d_rule, stream):
         """Bytes the graph's workspace needs.  The query for an unweighted graph may hold 8 bytes per entry that
-        are used only where rows of degree > d_rule have less than 2% of the entries.  Where that is 256 MB or
-        more and they have more, the weighted graph's size, which is without, does (three small kernels and a
-        wait against a creation of tens of milliseconds)."""
+        are used only where rows of degree > d_rule have less than 2% of the entries.  Where that is 8 GB or more
+        (3% of the card) and they have more, the weighted graph's size, which is without, does (three small
+        kernels and a wait against a creation of hundreds of milliseconds)."""
         ws, wsw = C.c_size_t(), C.c_size_t()
         check(lib().n2v_graph_workspace(self.n, self.m, int(self.wt is not None), C.byref(ws)), "n2v_graph_workspace")
-        if self.wt is None and self.m >= 1 << 25 and stream is None:
+        if self.wt is None and self.m >= TRIM_ENTRIES and stream is None:
             check(lib().n2v_graph_workspace(self.n, self.m, 1, C.byref(wsw)), "n2v_graph_workspace")
             if wsw.value < ws.value:
                 off = self.off.view(_torch().int64)
